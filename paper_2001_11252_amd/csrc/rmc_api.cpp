@@ -1049,15 +1049,14 @@ rmc_status layout_queue(rmc_ctx *c, unsigned long long n_regions) {
   const unsigned long long max_cap =
       std::max<unsigned long long>(PQ_MAX_BYTES / peel_job_bytes(c->precision == RMC_FP32_BULK) / n_regions, PQ_FIRST_CAP);
   c->pq_cap = std::min(c->pq_cap, max_cap);
-  HIPCHK(c, c->pq_counts.ensure(n_regions * 4));
+  HIPCHK(c, c->pq_counts.ensure((2 * n_regions + 1) * 4));   // counts, then their running sums
   HIPCHK(c, c->pq_jobs.ensure(n_regions * c->pq_cap * peel_job_bytes(c->precision == RMC_FP32_BULK)));
   PeelQueue q;
   q.jobs = c->pq_jobs.p;
   q.counts = c->pq_counts.as<uint32_t>();
+  q.offs = q.counts + n_regions;
   q.cap = c->pq_cap;
   q.n_regions = n_regions;
-  q.pushes = 0;
-  q.max_region = 0;
   q.take = 0;
   q.lost = 0;
   HIPCHK(c, hipMemcpyAsync(c->pq_ctl.p, &q, sizeof q, hipMemcpyHostToDevice, c->stream));
@@ -1146,7 +1145,7 @@ rmc_status stream_open(rmc_ctx *c, int64_t total, int n_probs, int levels, bool 
       } else {
         const int grid = c->num_cus * peel_drain_blocks_per_cu(f32, batch, c->s_one_line, c->s_levels);
         if (e == hipSuccess)
-          e = launch_peel_drain(f32, batch, c->s_one_line, c->s_probs, pq, c->s_levels, grid,
+          e = launch_peel_drain(f32, batch, c->s_one_line, c->s_probs, pq, (int)(n_slots / 64), c->s_levels, grid,
                                 c->d_slice.as<unsigned long long>(),
                                 cap);
       }
@@ -1212,8 +1211,6 @@ rmc_status stream_step(rmc_ctx *c, rmc_run_stats *slice, int64_t *remaining) {
     // the captured launches with the grid of the gathered slots
     const bool f32 = c->precision == RMC_FP32_BULK;
     HIPCHK(c, launch_fill_u64(c->d_slice.as<unsigned long long>(), N_STATS + 3, 0ull, c->stream));
-    // regions of waves not launched must read empty in the pass
-    if (c->s_pq) HIPCHK(c, launch_fill_u32(c->pq_counts.as<uint32_t>(), (int64_t)c->pq_regions, 0u, c->stream));
     // at most one wave per SIMD: the kernel compiled for one (no spills)
     const bool lone = (int64_t)c->s_tail_grid * (c->block / 64) <= (int64_t)c->num_cus * 4;
     HIPCHK(c, launch_transport(f32, c->s_batch, c->s_defer, c->s_one_line, c->regroup != 0, c->s_probs,
@@ -1223,7 +1220,8 @@ rmc_status stream_step(rmc_ctx *c, rmc_run_stats *slice, int64_t *remaining) {
     HIPCHK(c, hipEventRecord(c->ev1, c->stream));
     if (c->s_pq) {
       const int grid = c->num_cus * peel_drain_blocks_per_cu(f32, c->s_batch, c->s_one_line, c->s_levels);
-      HIPCHK(c, launch_peel_drain(f32, c->s_batch, c->s_one_line, c->s_probs, c->s_pq, c->s_levels, grid,
+      HIPCHK(c, launch_peel_drain(f32, c->s_batch, c->s_one_line, c->s_probs, c->s_pq,
+                                  c->s_tail_grid * (c->block / 64), c->s_levels, grid,
                                   c->d_slice.as<unsigned long long>(), c->stream));
     }
   } else {

@@ -103,11 +103,10 @@ constexpr unsigned long long PQ_ELEM_MASK = (1ull << PQ_OBS_SHIFT) - 1ull;
 struct PeelQueue {
   void *jobs;                     // PeelJob<R> [n_regions][cap]: one region per transport wave
   uint32_t *counts;               // [n_regions]: pushes of each region in the last launch
+  uint32_t *offs;                 // [n_regions + 1]: jobs queued in the regions before each one
   unsigned long long cap;         // jobs per region (a wave stops its slice before it)
-  unsigned long long n_regions;
-  unsigned long long pushes;      // pushes of the launch
-  unsigned long long max_region;  // largest region push count of the launch
-  unsigned long long take;        // regions handed out by the ray-cast pass
+  unsigned long long n_regions;   // regions of the last launch's waves (set by k_peel_scan)
+  unsigned long long take;        // jobs handed out by the ray-cast pass
   unsigned long long lost;        // pushes that found their region full (an error)
 };
 

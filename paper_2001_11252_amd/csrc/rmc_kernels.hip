@@ -8,8 +8,8 @@
 //               peel-off ray is decided in the scattering's own leaf or
 //               queued in the wave's region of the peel-off queue.
 // k_peel_drain  ray-cast pass over the queued peel-off rays after each
-//               transport launch (lanes refilled per ray), k_peel_reset
-//               its bookkeeping
+//               transport launch (lanes refilled per ray), k_peel_scan
+//               the index of its jobs
 // k_trace       deterministic cell sequence of rays (probe)
 // k_tau         optical depth of rays to the domain border (probe)
 // k_image_fwd   peel-off image of fixed rays
@@ -1008,12 +1008,7 @@ __global__ void __launch_bounds__(256)
     q.active = 0;
   }
   if (queue && lane == 0) {
-    const int nq = *snk.count;
-    pq->counts[wave] = (uint32_t)nq;
-    if (nq) {
-      atomicAdd(&pq->pushes, (unsigned long long)nq);
-      atomicMax(&pq->max_region, (unsigned long long)nq);
-    }
+    pq->counts[wave] = (uint32_t)*snk.count;
   }
   unsigned long long v[5] = {acc.scat, acc.dust, acc.cross, acc.peel_rays, acc.peel_cross};
   const int idx[5] = {S_SCAT, S_DUST_SCAT, S_CROSS, S_PEEL_RAYS, S_PEEL_CROSS};
@@ -1061,15 +1056,78 @@ __global__ void k_compact_slots(const SlotState *__restrict__ src, int64_t n, Sl
   if (act) dst[base + (unsigned long long)__popcll(m & ((1ull << lane) - 1ull))] = src[i];
 }
 
-__global__ void k_fill_u32(uint32_t *p, int64_t n, uint32_t v) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = v;
+// Before the ray-cast pass: offs[r] = jobs queued in regions 0 .. r - 1 of the
+// launch's n_regions waves, so that the pass can hand out its jobs by one
+// running index whatever the regions hold.  Reports the launch's pushes, its
+// fullest region and its lost pushes (slice counters N_STATS .. N_STATS + 2)
+// and resets the queue's totals.  One block: a few thousand counts.
+__global__ void __launch_bounds__(1024) k_peel_scan(PeelQueue *pq, int n_regions, unsigned long long *slice) {
+  __shared__ uint32_t part[16], top[16];
+  const int lane = __lane_id(), wave = threadIdx.x >> 6;
+  const uint32_t cap = (uint32_t)pq->cap;
+  uint32_t base = 0, most = 0;
+  for (int b = 0; b < n_regions; b += 1024) {
+    const int r = b + (int)threadIdx.x;
+    const uint32_t c = r < n_regions ? pq->counts[r] : 0u;
+    most = c > most ? c : most;
+    const uint32_t v = c < cap ? c : cap;
+    uint32_t x = v;
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t y = __shfl_up(x, off);
+      if (lane >= off) x += y;
+    }
+    if (lane == 63) part[wave] = x;
+    __syncthreads();
+    uint32_t before = base, all = base;
+    for (int w = 0; w < 16; ++w) {
+      if (w < wave) before += part[w];
+      all += part[w];
+    }
+    if (r < n_regions) pq->offs[r] = before + x - v;
+    base = all;
+    __syncthreads();
+  }
+  for (int off = 32; off > 0; off >>= 1) {
+    const uint32_t y = __shfl_xor(most, off);
+    most = y > most ? y : most;
+  }
+  if (lane == 0) top[wave] = most;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 16; ++w) most = top[w] > most ? top[w] : most;
+    pq->offs[n_regions] = base;
+    pq->n_regions = (unsigned long long)n_regions;
+    slice[N_STATS] = base;
+    slice[N_STATS + 1] = most;
+    slice[N_STATS + 2] = pq->lost;
+    pq->lost = 0ull;
+    pq->take = 0ull;
+  }
+}
+
+// The region holding queued job j: the last r with offs[r] <= j (j < offs[n]).
+// The wave's lanes test 64 regions at a time, so 4096 regions take two loads.
+__device__ __forceinline__ uint32_t region_of(const uint32_t *__restrict__ offs, uint32_t n, uint32_t j, int lane) {
+  uint32_t lo = 0;
+  while (n > 1) {
+    const uint32_t step = (n + 63) / 64;
+    const uint32_t i = (uint32_t)lane * step;
+    const unsigned long long m = __ballot(i < n && offs[lo + i] <= j);
+    const uint32_t k = (uint32_t)(__popcll(m) - 1) * step;
+    lo += k;
+    n = n - k < step ? n - k : step;
+  }
+  return lo;
 }
 
 // Ray-cast pass over the peel-off rays queued by a transport launch.  A
-// wave takes the queue regions one at a time; each lane walks one ray a
-// leaf per iteration and takes the region's next ray as soon as its own is
-// done, so the waves stay full while ray lengths vary.  The walk is the one
+// wave takes runs of queued jobs by their running index over all regions
+// (k_peel_scan), so the pass spreads over the chip also where a few waves
+// queued every ray, as at the end of a run (handing a wave a whole region
+// left a complete 2e5-packet run of the dusty sphere at tau0 = 5e3 with
+// 208 ms of this pass out of 340 ms; it now takes 172 ms in all); each lane
+// walks one ray a leaf per iteration and takes the run's next ray as soon as
+// its own is done, so the waves stay full while ray lengths vary.  The walk is the one
 // of ray_walk from the queued state (a ray's start, or where it left its
 // first leaf), and every deferred deposit is made here.
 #ifndef RMC_DRAIN_WAVES_F32
@@ -1090,13 +1148,19 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DrainW
   const int stride = blockDim.x;
   int *stk = lds + threadIdx.x;
   const int lane = __lane_id();
-  const unsigned long long n_regions = pq->n_regions, cap = pq->cap;
+  const unsigned long long cap = pq->cap;
+  const uint32_t n_regions = (uint32_t)pq->n_regions;
   const PeelJob<R> *__restrict__ jobs = (const PeelJob<R> *)pq->jobs;
-  const uint32_t *__restrict__ counts = pq->counts;
+  const uint32_t *__restrict__ offs = pq->offs;
+  const uint32_t total = offs[n_regions];
+  // jobs a wave takes at once: enough to spread what the take and its
+  // region search cost, few enough that the waves end together
+  const uint32_t share = total / (gridDim.x * (blockDim.x / 64) * 8u);
+  const uint32_t run = share < 64u ? 64u : (share > 1024u ? 1024u : share);
   const double cut = TauCut<R>::v;
-  // wave-uniform: current region, next job in it, jobs in it
-  unsigned long long reg = 0;
-  uint32_t r_next = 0, r_n = 0;
+  // wave-uniform: next job and end of the wave's run, the region of the next
+  // job, its first job and its end (running indices)
+  uint32_t cur = 0, end = 0, reg = 0, r_beg = 0, r_end = 0;
   bool drained = false;
   bool active = false;
   int prob = 0, acc_prob = 0;
@@ -1111,24 +1175,28 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DrainW
   while (true) {
     unsigned long long idle = __ballot(!active);
     while (idle && !drained) {
-      if (r_next >= r_n) {
+      if (cur >= end) {
         unsigned long long t = 0;
-        if (lane == 0) t = atomicAdd(&pq->take, 1ull);
-        reg = __shfl(t, 0);
-        if (reg >= n_regions) {
+        if (lane == 0) t = atomicAdd(&pq->take, (unsigned long long)run);
+        t = __shfl(t, 0);
+        if (t >= total) {
           drained = true;
           break;
         }
-        const uint32_t cnt = counts[reg];
-        r_n = cnt < cap ? cnt : (uint32_t)cap;
-        r_next = 0;
-        continue;
+        cur = (uint32_t)t;
+        end = total - cur < run ? total : cur + run;
+        r_end = 0;
       }
-      const uint32_t avail = r_n - r_next;
+      if (cur >= r_end) {
+        reg = region_of(offs, n_regions, cur, lane);
+        r_beg = offs[reg];
+        r_end = offs[reg + 1];
+      }
+      const uint32_t avail = (end < r_end ? end : r_end) - cur;
       const uint32_t rank = (uint32_t)__popcll(idle & ((1ull << lane) - 1ull));
       const bool mine = ((idle >> lane) & 1ull) && rank < avail;
       if (mine) {
-        const PeelJob<R> j = jobs[reg * cap + r_next + rank];
+        const PeelJob<R> j = jobs[reg * cap + (cur - r_beg) + rank];
         const int jp = BATCH ? (int)(j.dst >> PQ_PROB_SHIFT) : 0;
         if (BATCH && jp != acc_prob) {
           if (nc_prob) atomicAdd(probs[acc_prob].stats + S_PEEL_CROSS, nc_prob);
@@ -1175,7 +1243,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DrainW
         }
       }
       const uint32_t n_idle = (uint32_t)__popcll(idle);
-      r_next += avail < n_idle ? avail : n_idle;
+      cur += avail < n_idle ? avail : n_idle;
       // lanes given a job that ended at once stay idle until the next pass
       idle &= ~__ballot(mine);
     }
@@ -1242,20 +1310,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DrainW
   }
   if (lane == 0 && v) atomicAdd(slice + S_PEEL_CROSS, v);
   if (lane == 0 && d) atomicAdd(slice + S_PEEL_DROPPED, d);
-}
-
-// After the ray-cast pass: report the launch's pushes, largest region and
-// lost pushes (slice counters N_STATS .. N_STATS+2) and reset the totals.
-__global__ void k_peel_reset(PeelQueue *pq, unsigned long long *slice) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    slice[N_STATS] = pq->pushes;
-    slice[N_STATS + 1] = pq->max_region;
-    slice[N_STATS + 2] = pq->lost;
-    pq->lost = 0ull;
-    pq->pushes = 0ull;
-    pq->max_region = 0ull;
-    pq->take = 0ull;
-  }
 }
 
 // ------------------------------------------------------------------ probes
@@ -1850,13 +1904,13 @@ static DrainFn drain_fn(bool fp32, bool batch, bool one_line) {
 }
 
 hipError_t launch_peel_drain(bool fp32, bool batch, bool one_line, const ProblemK *d_probs, void *pq,
-                             int stack_levels, int grid, unsigned long long *slice, hipStream_t st) {
+                             int n_regions, int stack_levels, int grid, unsigned long long *slice, hipStream_t st) {
   const int b = 256;
   const size_t lds = (size_t)stack_levels * b * sizeof(int);
   PeelQueue *q = (PeelQueue *)pq;
-  hipLaunchKernelGGL(drain_fn(fp32, batch, one_line), dim3(grid), dim3(b), lds, st, d_probs, q, slice);
+  hipLaunchKernelGGL(k_peel_scan, dim3(1), dim3(1024), 0, st, q, n_regions, slice);
   if (hipError_t e = hipGetLastError()) return e;
-  hipLaunchKernelGGL(k_peel_reset, dim3(1), dim3(64), 0, st, q, slice);
+  hipLaunchKernelGGL(drain_fn(fp32, batch, one_line), dim3(grid), dim3(b), lds, st, d_probs, q, slice);
   return hipGetLastError();
 }
 
@@ -1892,12 +1946,6 @@ hipError_t launch_compact_slots(const void *src, int64_t n, void *dst, unsigned 
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_compact_slots, dim3(blocks_for(n, 256)), dim3(256), 0, st, (const SlotState *)src, n,
                      (SlotState *)dst, n_live);
-  return hipGetLastError();
-}
-
-hipError_t launch_fill_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_fill_u32, dim3(blocks_for(n, 256)), dim3(256), 0, st, p, n, v);
   return hipGetLastError();
 }
 

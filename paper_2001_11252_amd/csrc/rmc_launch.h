@@ -19,10 +19,11 @@ hipError_t launch_transport(bool fp32, bool batch, bool defer, bool one_line, bo
                             int stack_levels, int grid, int block, void *slots, int budget,
                             unsigned long long *slice, hipStream_t st, bool tail = false);
 size_t slot_bytes();
-// Ray-cast pass over the peel-off queue pq (a device PeelQueue), then the
-// queue reset; grid blocks of 256 threads.
+// Index of the jobs in the peel-off queue pq (a device PeelQueue) whose first
+// n_regions regions the last transport launch filled, then the ray-cast pass
+// over them; grid blocks of 256 threads.
 hipError_t launch_peel_drain(bool fp32, bool batch, bool one_line, const ProblemK *d_probs, void *pq,
-                             int stack_levels, int grid, unsigned long long *slice, hipStream_t st);
+                             int n_regions, int stack_levels, int grid, unsigned long long *slice, hipStream_t st);
 int peel_drain_blocks_per_cu(bool fp32, bool batch, bool one_line, int stack_levels);
 size_t peel_job_bytes(bool fp32);
 size_t peel_queue_bytes();
@@ -33,7 +34,6 @@ hipError_t launch_count_live(const void *slots, int64_t n, unsigned long long *o
 // active slots of src[0, n) copied to distinct slots of dst; *n_live += their count
 hipError_t launch_compact_slots(const void *src, int64_t n, void *dst, unsigned long long *n_live,
                                 hipStream_t st);
-hipError_t launch_fill_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t st);
 hipError_t launch_trace(const ProblemK &pb, int64_t n, const double *orig, const double *dir,
                         int max_cells, int32_t *leaf, double *seg, int32_t *cnt, hipStream_t st);
 hipError_t launch_tau(bool fp32, const ProblemK &pb, int64_t n, const double *orig, const double *dir,
