@@ -145,7 +145,7 @@ struct rmc_ctx {
   DevBuf slots, d_slice;
   DevBuf slots2, d_live;     // gathered slots (tail of a stream) and their count
   int s_tail_grid = 0;       // >0: blocks of the launches on gathered slots
-  int64_t s_total = 0, s_done = 0;
+  int64_t s_total = 0, s_started = 0, s_done = 0;
   int s_grid = 0, s_levels = 1, s_nprobs = 0;
   bool s_open = false, s_batch = false;
   const ProblemK *s_probs = nullptr;
@@ -526,7 +526,6 @@ rmc_status ensure_outputs(rmc_ctx *c, int64_t n, hipStream_t st) {
   HIPCHK(c, c->o_pos.ensure(m * 24));
   HIPCHK(c, c->o_path.ensure(m * 8));
   HIPCHK(c, c->d_stats.ensure(N_STATS * 8));
-  HIPCHK(c, c->d_next.ensure(8));
   if (n > 0) HIPCHK(c, hipMemsetAsync(c->o_status.p, 0, (size_t)n * 4, st));
   return RMC_OK;
 }
@@ -1096,7 +1095,7 @@ rmc_status grow_queue(rmc_ctx *c, unsigned long long max_region) {
 rmc_status stream_open(rmc_ctx *c, int64_t total, int n_probs, int levels, bool batch) {
   c->image_done = false;
   c->s_total = total;
-  c->s_done = 0;
+  c->s_started = c->s_done = 0;
   c->s_nprobs = n_probs;
   c->s_levels = std::max(levels, 1);
   c->s_batch = batch;
@@ -1104,22 +1103,24 @@ rmc_status stream_open(rmc_ctx *c, int64_t total, int n_probs, int levels, bool 
   c->s_tail_grid = 0;
   const int64_t n_slots = (int64_t)c->s_grid * c->block;
   HIPCHK(c, c->slots.ensure((size_t)n_slots * slot_bytes()));
-  HIPCHK(c, c->d_slice.ensure((N_STATS + 3) * 8));
-  HIPCHK(c, c->d_next.ensure(8));
+  HIPCHK(c, c->d_slice.ensure((N_STATS + 4) * 8));
+  const int n_waves = (int)(n_slots / 64);
+  HIPCHK(c, c->d_next.ensure((RESERVE_OFFSET + 2 * (size_t)n_waves) * 8));
   HIPCHK(c, launch_clear_slots(c->slots.p, n_slots, c->stream));
   if (c->s_pq) {
     rmc_status r = layout_queue(c, (unsigned long long)n_slots / 64);
     if (r) return r;
   }
-  HIPCHK(c, launch_batch_reset(c->s_probs, n_probs, c->d_next.as<unsigned long long>(), c->stream));
+  HIPCHK(c, launch_batch_reset(c->s_probs, n_probs, c->d_next.as<unsigned long long>(), n_waves,
+                               c->stream));
   std::memset(&c->s_acc, 0, sizeof c->s_acc);
   c->s_open = true;
   // one slice = zero the slice counters, one transport launch; captured
   // once per shape and replayed
   char key[256];
   PeelQueue *pq = c->s_pq;
-  snprintf(key, sizeof key, "%p/%p/%p/%p/%p/%d/%d/%d/%d/%d/%d/%d/%d/%d", (void *)c->s_probs, (void *)c->s_starts,
-           c->slots.p, c->d_slice.p, (void *)pq, n_probs, c->s_grid, c->block, c->refill, c->s_levels,
+  snprintf(key, sizeof key, "%p/%p/%p/%p/%p/%p/%d/%d/%d/%d/%d/%d/%d/%d/%d", (void *)c->s_probs, (void *)c->s_starts,
+           c->slots.p, c->d_slice.p, c->d_next.p, (void *)pq, n_probs, c->s_grid, c->block, c->refill, c->s_levels,
            c->precision, c->slice_iters, (int)batch,
            (int)c->regroup * 4 + (int)c->s_one_line * 2 + (int)c->s_defer);
   if (c->s_key != key || !c->s_graph) {
@@ -1136,7 +1137,7 @@ rmc_status stream_open(rmc_ctx *c, int64_t total, int n_probs, int levels, bool 
       hipGraph_t g = nullptr;
       e = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
       if (part == 0) {
-        if (e == hipSuccess) e = launch_fill_u64(c->d_slice.as<unsigned long long>(), N_STATS + 3, 0ull, cap);
+        if (e == hipSuccess) e = launch_fill_u64(c->d_slice.as<unsigned long long>(), N_STATS + 4, 0ull, cap);
         if (e == hipSuccess)
           e = launch_transport(f32, batch, c->s_defer, c->s_one_line, c->regroup != 0, c->s_probs, c->s_starts,
                                n_probs,
@@ -1210,7 +1211,7 @@ rmc_status stream_step(rmc_ctx *c, rmc_run_stats *slice, int64_t *remaining) {
   if (c->s_tail_grid > 0) {
     // the captured launches with the grid of the gathered slots
     const bool f32 = c->precision == RMC_FP32_BULK;
-    HIPCHK(c, launch_fill_u64(c->d_slice.as<unsigned long long>(), N_STATS + 3, 0ull, c->stream));
+    HIPCHK(c, launch_fill_u64(c->d_slice.as<unsigned long long>(), N_STATS + 4, 0ull, c->stream));
     // at most one wave per SIMD: the kernel compiled for one (no spills)
     const bool lone = (int64_t)c->s_tail_grid * (c->block / 64) <= (int64_t)c->num_cus * 4;
     HIPCHK(c, launch_transport(f32, c->s_batch, c->s_defer, c->s_one_line, c->regroup != 0, c->s_probs,
@@ -1230,9 +1231,8 @@ rmc_status stream_step(rmc_ctx *c, rmc_run_stats *slice, int64_t *remaining) {
     if (c->s_pq) HIPCHK(c, hipGraphLaunch(c->s_graph2, c->stream));
   }
   HIPCHK(c, hipEventRecord(c->ev2, c->stream));
-  unsigned long long h[N_STATS + 3], next = 0;
+  unsigned long long h[N_STATS + 4];
   HIPCHK(c, hipMemcpyAsync(h, c->d_slice.p, sizeof h, hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(c, hipMemcpyAsync(&next, c->d_next.p, 8, hipMemcpyDeviceToHost, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   float ms = 0.f, ms2 = 0.f;
   HIPCHK(c, hipEventElapsedTime(&ms, c->ev0, c->ev1));
@@ -1250,10 +1250,11 @@ rmc_status stream_step(rmc_ctx *c, rmc_run_stats *slice, int64_t *remaining) {
     if (r) return r;
   }
   c->s_done += (int64_t)h[S_EMITTED];
+  c->s_started += (int64_t)h[N_STATS + 3];
   add_run_stats(c->s_acc, z);
   if (slice) *slice = z;
   if (remaining) *remaining = c->s_total - c->s_done;
-  if (c->compact && (int64_t)next >= c->s_total && c->s_done < c->s_total) {
+  if (c->compact && c->s_started >= c->s_total && c->s_done < c->s_total) {
     rmc_status r = gather_tail(c);
     if (r) return r;
   }

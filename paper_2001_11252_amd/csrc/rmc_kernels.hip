@@ -3,8 +3,8 @@
 // k_transport   persistent per-packet propagation loop (Sect. 3, 3.2, 4.3)
 //               with peel-off toward observers at each emission and
 //               scattering (Sect. 5.1); one packet per lane, lanes of a
-//               wave refilled from a global queue with one atomic per wave
-//               (ballot + mbcnt compaction of the idle lanes).  Each
+//               wave refilled from the wave's reserve of a global queue
+//               (ballot + mbcnt ranks of the idle lanes).  Each
 //               peel-off ray is decided in the scattering's own leaf or
 //               queued in the wave's region of the peel-off queue.
 // k_peel_drain  ray-cast pass over the queued peel-off rays after each
@@ -386,20 +386,18 @@ template <class R> __device__ __forceinline__ void set_geom_dir(Lane<R> &s) {
   }
 }
 
-// Record a packet that ended (escaped, absorbed or stuck): its outputs, its
-// counts in the problem's totals, and, in the launch's slice counters, the
-// packet and its status (its dropped peel-off deposits are reported in the
-// slice where it ends).
-// Record a finished packet and count it.  The counts of the lanes that
-// finish here together are summed over the wave first, one atomic per
-// counter and wave: packets that end at once (short walks, a whole wave of
-// them per loop pass) would otherwise queue on the same few addresses, one
-// atomic per packet and counter.  Single-problem launches publish the
-// packets' work (scatterings, crossings, peel-off rays) with the launch's
-// slice totals at the end of the kernel; in batches, whose lanes change
-// problem, each packet adds its own to its problem's totals here.
+// Record a packet that ended (escaped, absorbed or stuck): its outputs and
+// its counts.  Ends are counted in the wave's LDS counters ends[status - 1]
+// and published once per launch: with an atomic on the run's counters per
+// wave and loop pass, packets with short walks queued on those few addresses
+// (the Fe II wind, 2e6 packets: four such atomics and one on the queue per
+// group of ends took most of 24.7 ms; 3.8 ms without them).  Single-problem launches publish the packets' work (scatterings,
+// crossings, peel-off rays) with the launch's slice totals at the end of the
+// kernel; in batches, whose lanes change problem, each packet adds its own
+// to its problem's totals here.  Dropped peel-off deposits are reported in
+// the slice where their packet ends.
 template <class R, bool BATCH>
-__device__ void finish(const ProblemK &pb, Lane<R> &s, int status, unsigned long long *slice) {
+__device__ void finish(const ProblemK &pb, Lane<R> &s, int status, int *ends, unsigned long long *slice) {
   const int64_t i = s.pid - pb.first;
   pb.status[i] = status;
   pb.x_out[i] = (double)s.x;
@@ -412,25 +410,10 @@ __device__ void finish(const ProblemK &pb, Lane<R> &s, int status, unsigned long
   pb.nscat[i] = s.nscat;
   pb.path_out[i] = s.path;
   unsigned long long *st = pb.stats;
-  const int sk = status == ST_ESCAPED ? S_ESCAPED : (status == ST_ABSORBED ? S_ABSORBED : S_STUCK);
-  const unsigned long long m = __ballot(true);
-  const unsigned long long me = __ballot(status == ST_ESCAPED), ma = __ballot(status == ST_ABSORBED);
-  const unsigned long long ms = m & ~(me | ma);
-  if (__lane_id() == __ffsll((long long)m) - 1) {
-    atomicAdd(slice + S_EMITTED, (unsigned long long)__popcll(m));
-    if (me) atomicAdd(slice + S_ESCAPED, (unsigned long long)__popcll(me));
-    if (ma) atomicAdd(slice + S_ABSORBED, (unsigned long long)__popcll(ma));
-    if (ms) atomicAdd(slice + S_STUCK, (unsigned long long)__popcll(ms));
-    if (!BATCH) {
-      atomicAdd(st + S_EMITTED, (unsigned long long)__popcll(m));
-      if (me) atomicAdd(st + S_ESCAPED, (unsigned long long)__popcll(me));
-      if (ma) atomicAdd(st + S_ABSORBED, (unsigned long long)__popcll(ma));
-      if (ms) atomicAdd(st + S_STUCK, (unsigned long long)__popcll(ms));
-    }
-  }
+  atomicAdd(ends + (status - 1), 1);
   if (BATCH) {
     atomicAdd(st + S_EMITTED, 1ull);
-    atomicAdd(st + sk, 1ull);
+    atomicAdd(st + S_ESCAPED + (status - 1), 1ull);
     atomicAdd(st + S_SCAT, (unsigned long long)s.nscat);
     if (s.cnt.dust_scat) atomicAdd(st + S_DUST_SCAT, (unsigned long long)s.cnt.dust_scat);
     atomicAdd(st + S_CROSS, (unsigned long long)s.cnt.cross);
@@ -795,6 +778,13 @@ __device__ __forceinline__ void add_delta(SliceCount &a, const Lane<R> &s, const
   a.peel_cross += s.cnt.peel_cross - z.cnt.peel_cross;
 }
 
+// The first active lane's value, as a wave-uniform one.
+__device__ __forceinline__ unsigned long long uniform64(unsigned long long v) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+  return (unsigned long long)hi << 32 | lo;
+}
+
 // Waves per SIMD the transport kernel is compiled for (register budget,
 // chosen by measurement): the float single-problem kernels with deferred
 // peel-off run four (about 30 registers spill with one line, 40 with four,
@@ -804,6 +794,18 @@ __device__ __forceinline__ void add_delta(SliceCount &a, const Lane<R> &s, const
 // two (40-55 registers spill, and the dusty sphere runs 38% faster than at
 // one, where nothing spills), the other double kernels (batch, inline
 // walker; 90-200 registers would spill at two) one.
+// Idle lane passes a wave gathers before it records its ended packets and
+// takes new ones.  A refill (emission, point location, the ended packets'
+// outputs) costs the wave about as many instructions as one loop pass does
+// for its 64 lanes whether one lane or all take part, so waiting until 64
+// lane passes were idle at most doubles the smaller of the two costs (the
+// Fe II wind, 2e6 packets of 48 crossings: 5.6 ms without the wait, 3.9 at
+// 24, 3.8 at 64 and 128; long walks: no difference).
+#ifndef RMC_REFILL_DEBT
+#define RMC_REFILL_DEBT 64
+#endif
+constexpr uint32_t REFILL_DEBT = RMC_REFILL_DEBT;
+
 #ifndef RMC_WAVES_F32_LEAN
 #define RMC_WAVES_F32_LEAN 4
 #endif
@@ -834,7 +836,8 @@ template <bool BATCH, bool DEFER, int NL> struct WavesPerEU<double, BATCH, DEFER
 // TAIL: the same kernel compiled for one wave per SIMD (registers to spare,
 // no spills), for the launches over gathered slots at the end of a run,
 // whose waves are no more than the SIMDs: each issues on its own, so its
-// latency, not the chip's throughput, sets the pace.
+// latency, not the chip's throughput, sets the pace.  Every packet has
+// started by then: it holds no refill.
 template <class R, bool BATCH, bool DEFER, int NL, bool REGROUP = false, bool TAIL = false>
 __global__ void __launch_bounds__(256)
     __attribute__((amdgpu_waves_per_eu(TAIL ? 1 : WavesPerEU<R, BATCH, DEFER, NL>::v,
@@ -858,21 +861,33 @@ __global__ void __launch_bounds__(256)
   // (no queue when no problem of the launch has an observer)
   PeelQueue *const pq = DEFER ? probs[0].pq : nullptr;
   const bool queue = DEFER && pq != nullptr;
-  const int64_t wave = gid >> 6;
+  // (wave-uniform, and told so: what follows from it then stays in scalar registers)
+  const int wib = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t wave = (int64_t)blockIdx.x * (stride >> 6) + wib;
   PeelSink<R> snk;
-  snk.count = lds + 2 * stack_levels * stride + (threadIdx.x >> 6);
+  // per wave: queued rays, then the packets that escaped, were absorbed, got stuck
+  int *const wcnt = lds + 2 * stack_levels * stride + 4 * wib;
+  snk.count = wcnt;
   snk.region = queue ? (PeelJob<R> *)pq->jobs + (size_t)wave * pq->cap : nullptr;
   snk.cap = queue ? (uint32_t)pq->cap : 0u;
   snk.lost = queue ? &pq->lost : nullptr;
   const int room = queue ? (int)pq->cap - 2 * 64 * MAX_OBS : 0x7fffffff;
-  if (lane == 0) *snk.count = 0;
+  if (lane < 4) wcnt[lane] = 0;
+
+  // the wave's reserve of packets taken from the queue and not started yet
+  unsigned long long *const reserve = next + RESERVE_OFFSET + 2 * wave;
+  unsigned long long r_next = uniform64(reserve[0]), r_end = uniform64(reserve[1]);
+  bool plenty = false;   // enough packets left in the queue for every wave to take more than it needs
+  uint32_t started = 0;
 
   Lane<R> s;
   Lane<R> z;            // counters when this slice took the packet over
   SliceCount acc{0, 0, 0, 0, 0};
   int prob = 0;
   bool active = false;
+  int fin = ST_NONE;     // status of a packet that has ended and is not recorded yet
   bool drained = false;
+  uint32_t debt = 0;     // idle lane passes since the last refill
   {
     const SlotState &q = slots[gid];
     if (q.active) {
@@ -887,50 +902,73 @@ __global__ void __launch_bounds__(256)
   }
   for (int it = 0; it < budget; ++it) {
     if (DEFER && *snk.count > room) break;
-    // ---- refill idle lanes: one atomic per wave, ranks from mbcnt
-    if (!drained) {
-      const unsigned long long idle = __ballot(!active);
-      const int n_idle = __popcll(idle);
-      const bool any_active = idle != ~0ull >> (64 - warpSize);
-      if (n_idle > 0 && (n_idle >= refill_min || !any_active)) {
-        unsigned long long base = 0;
-        if (lane == __ffsll((long long)idle) - 1) base = atomicAdd(next, (unsigned long long)n_idle);
-        base = __shfl(base, __ffsll((long long)idle) - 1);
-        if (base >= (unsigned long long)total) drained = true;
-        if (!active) {
-          const unsigned long long below = idle & ((1ull << lane) - 1ull);
-          const int64_t g = (int64_t)(base + __popcll(below));
-          if (g < total) {
-            if (BATCH) {
-              int lo = 0, hi = n_probs - 1;
-              while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (starts[mid] <= g) lo = mid; else hi = mid - 1;
-              }
-              prob = lo;
-            }
-            const ProblemK &pb = probs[BATCH ? prob : 0];
-            const int64_t pid = pb.first + (g - starts[BATCH ? prob : 0]);
-            emit<R, DEFER, NL>(pb, pid, s, stk, pstk, stride, snk);
-            z = s;
-            z.nscat = 0;
-            z.cnt = LaneCount{0, 0, 0, 0, 0};
-            int X[3];
-            if (int_coords(pb.L, s.p, s.kd, X)) {
-              locate(pb, X, stk, stride, s.c);
-              s.lf = load_leaf<R>(pb.leaves, s.c.leaf);
-              active = true;
-            } else {
-              add_delta(acc, s, z);
-              finish<R, BATCH>(pb, s, ST_ESCAPED, slice);
-            }
-          }
+    // ---- record ended packets and refill idle lanes, together, once the
+    // lanes have idled about as much as that costs the wave (REFILL_DEBT
+    // lane passes), or none is active
+    const unsigned long long idle = __ballot(!active);
+    const uint32_t n_idle = (uint32_t)__popcll(idle);
+    const bool all_idle = n_idle == 64u;
+    if (TAIL && all_idle) break;   // every packet has started
+    if (!TAIL) debt += n_idle;
+    if (!TAIL && (all_idle || (!drained && debt >= REFILL_DEBT && (int)n_idle >= refill_min))) {
+      debt = 0;
+      if (fin != ST_NONE) {
+        add_delta(acc, s, z);
+        finish<R, BATCH>(probs[BATCH ? prob : 0], s, fin, wcnt + 1, slice);
+        fin = ST_NONE;
+      }
+      if (drained) break;
+      // packets from the wave's reserve, then from the queue; one atomic
+      // takes a wave's worth more than needed while the queue is long
+      const uint32_t have = (uint32_t)(r_end - r_next);
+      unsigned long long base = r_next, lim = r_end;
+      if (have < n_idle) {
+        const unsigned long long ask = n_idle - have + (plenty ? 64u : 0u);
+        if (lane == 0) base = atomicAdd(next, ask);
+        base = uniform64(base);
+        if (base >= (unsigned long long)total) {
+          drained = true;
+          base = lim = (unsigned long long)total;
+        } else {
+          lim = (unsigned long long)total - base < ask ? (unsigned long long)total : base + ask;
+          plenty = (unsigned long long)total - lim > (unsigned long long)gridDim.x * blockDim.x * 2u;
         }
       }
-    }
-    if (__ballot(active) == 0ull) {
-      if (drained) break;
-      continue;
+      const uint32_t rank = (uint32_t)__popcll(idle & ((1ull << lane) - 1ull));
+      const unsigned long long g =
+          have >= n_idle || rank < have ? r_next + rank : base + (rank - have);
+      const bool take = !active && (rank < have || g < lim);
+      started += (uint32_t)__popcll(__ballot(take));
+      if (have >= n_idle) {
+        r_next += n_idle;
+      } else {
+        r_next = lim - base < n_idle - have ? lim : base + (n_idle - have);
+        r_end = lim;
+      }
+      if (take) {
+        if (BATCH) {
+          int lo = 0, hi = n_probs - 1;
+          while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (starts[mid] <= (int64_t)g) lo = mid; else hi = mid - 1;
+          }
+          prob = lo;
+        }
+        const ProblemK &pb = probs[BATCH ? prob : 0];
+        const int64_t pid = pb.first + ((int64_t)g - starts[BATCH ? prob : 0]);
+        emit<R, DEFER, NL>(pb, pid, s, stk, pstk, stride, snk);
+        z = s;
+        z.nscat = 0;
+        z.cnt = LaneCount{0, 0, 0, 0, 0};
+        int X[3];
+        if (int_coords(pb.L, s.p, s.kd, X)) {
+          locate(pb, X, stk, stride, s.c);
+          s.lf = load_leaf<R>(pb.leaves, s.c.leaf);
+          active = true;
+        } else {
+          fin = ST_ESCAPED;
+        }
+      }
     }
     if (!active) continue;
 
@@ -994,10 +1032,13 @@ __global__ void __launch_bounds__(256)
       }
     }
     if (st != ST_NONE) {
-      add_delta(acc, s, z);
-      finish<R, BATCH>(pb, s, st, slice);
+      fin = st;
       active = false;
     }
+  }
+  if (fin != ST_NONE) {
+    add_delta(acc, s, z);
+    finish<R, BATCH>(probs[BATCH ? prob : 0], s, fin, wcnt + 1, slice);
   }
   // ---- park the packet (if any) for the next launch, publish the counts
   SlotState &q = slots[gid];
@@ -1009,6 +1050,24 @@ __global__ void __launch_bounds__(256)
   }
   if (queue && lane == 0) {
     pq->counts[wave] = (uint32_t)*snk.count;
+  }
+  if (lane == 0) {
+    reserve[0] = r_next;
+    reserve[1] = r_end;
+    if (started) atomicAdd(slice + N_STATS + 3, (unsigned long long)started);
+    unsigned long long n = 0;
+    for (int j = 1; j < 4; ++j) {
+      const unsigned long long e = (unsigned long long)(uint32_t)wcnt[j];
+      n += e;
+      if (e) {
+        atomicAdd(slice + S_ESCAPED + j - 1, e);
+        if (!BATCH) atomicAdd(probs[0].stats + S_ESCAPED + j - 1, e);
+      }
+    }
+    if (n) {
+      atomicAdd(slice + S_EMITTED, n);
+      if (!BATCH) atomicAdd(probs[0].stats + S_EMITTED, n);
+    }
   }
   unsigned long long v[5] = {acc.scat, acc.dust, acc.cross, acc.peel_rays, acc.peel_cross};
   const int idx[5] = {S_SCAT, S_DUST_SCAT, S_CROSS, S_PEEL_RAYS, S_PEEL_CROSS};
@@ -1798,12 +1857,12 @@ __global__ void k_hist(int64_t n, const int32_t *__restrict__ status, const doub
   if (b < nbins) atomicAdd(h + b, 1ull);
 }
 
-// Zero the counters of every problem of a launch and the work queue (a
-// kernel rather than a memset so that it can sit in a captured graph).
-__global__ void k_batch_reset(const ProblemK *__restrict__ probs, int n, unsigned long long *next) {
+// Zero the counters of every problem of a launch, the work queue and its
+// waves' reserves (a kernel rather than a memset so that it can sit in a captured graph).
+__global__ void k_batch_reset(const ProblemK *__restrict__ probs, int n, unsigned long long *next, int waves) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n * N_STATS) probs[i / N_STATS].stats[i % N_STATS] = 0ull;
-  if (i == 0) *next = 0ull;
+  if (i < RESERVE_OFFSET + 2 * waves) next[i] = 0ull;
 }
 
 __global__ void k_fill_u64(unsigned long long *p, int64_t n, unsigned long long v) {
@@ -1878,7 +1937,7 @@ static TransportFn transport_fn(bool fp32, bool batch, bool defer, bool one_line
 }
 
 static size_t transport_lds(int stack_levels, int block) {
-  return ((size_t)2 * stack_levels * block + block / 64) * sizeof(int);
+  return ((size_t)2 * stack_levels * block + 4 * (block / 64)) * sizeof(int);
 }
 
 hipError_t launch_transport(bool fp32, bool batch, bool defer, bool one_line, bool regroup, const ProblemK *d_probs,
@@ -2078,9 +2137,10 @@ hipError_t launch_hist(int64_t n, const int32_t *status, const double *x, int nb
   return hipGetLastError();
 }
 
-hipError_t launch_batch_reset(const ProblemK *d_probs, int n, unsigned long long *d_next, hipStream_t st) {
-  hipLaunchKernelGGL(k_batch_reset, dim3(blocks_for((int64_t)n * N_STATS, 256)), dim3(256), 0, st, d_probs, n,
-                     d_next);
+hipError_t launch_batch_reset(const ProblemK *d_probs, int n, unsigned long long *d_next, int waves,
+                              hipStream_t st) {
+  const int64_t m = (int64_t)n * N_STATS, w = RESERVE_OFFSET + 2 * (int64_t)waves;
+  hipLaunchKernelGGL(k_batch_reset, dim3(blocks_for(m > w ? m : w, 256)), dim3(256), 0, st, d_probs, n, d_next, waves);
   return hipGetLastError();
 }
 

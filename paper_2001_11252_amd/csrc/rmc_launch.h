@@ -76,7 +76,10 @@ constexpr int NOALLOC_MAX_BINS = 1 << 16;
 hipError_t scratch_address(int device, unsigned long long **out);
 hipError_t launch_hist(int64_t n, const int32_t *status, const double *x, int nbins, double x_min, double span,
                        unsigned long long *h, hipStream_t st);
-hipError_t launch_batch_reset(const ProblemK *d_probs, int n, unsigned long long *d_next, hipStream_t st);
+// d_next: the queue's next packet, then from word RESERVE_OFFSET on each of
+// `waves` waves' reserve [next, end).
+constexpr int RESERVE_OFFSET = 16;
+hipError_t launch_batch_reset(const ProblemK *d_probs, int n, unsigned long long *d_next, int waves, hipStream_t st);
 hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long v, hipStream_t st);
 hipError_t launch_u64_to_f64(const unsigned long long *a, double *b, int64_t n, hipStream_t st);
 hipError_t launch_f32_to_f64(const float *a, double *b, int64_t n, hipStream_t st);
