@@ -93,9 +93,13 @@ enum {
                                 launch that leaves at most three quarters of
                                 its lanes busy, and the next launches use
                                 only the waves they fill (the last, longest
-                                walks then run faster per wave); 0: every
-                                launch keeps the full grid.  The same packets
-                                either way.                                  */
+                                walks then run faster per wave); as soon as
+                                they fit one wave per SIMD, a kernel runs them
+                                whose waves hold few packets and compute their
+                                draws and peel-off with all lanes (runs of
+                                few packets from their first launch on); 0:
+                                every launch keeps the full grid.  The same
+                                packets either way.                          */
   RMC_OPT_VOIGT = 8          /* Voigt function H(a,x) of the opacity:
                                 0 (default) the Tasitsiomi form the paper
                                 uses (Sect. 3.3.2; within ~1% for Lya at

@@ -144,7 +144,10 @@ struct rmc_ctx {
   // streaming state (single problem or a batch led by this context)
   DevBuf slots, d_slice;
   DevBuf slots2, d_live;     // gathered slots (tail of a stream) and their count
+  void *s_slots = nullptr;   // the slots that hold the live packets (slots or slots2)
   int s_tail_grid = 0;       // >0: blocks of the launches on gathered slots
+  int s_walk_waves = 0;      // >0: waves of the walkers' launches (gathered slots)
+  int s_walk_lp = 0;         // log2 of the packets of each of them
   int64_t s_total = 0, s_started = 0, s_done = 0;
   int s_grid = 0, s_levels = 1, s_nprobs = 0;
   bool s_open = false, s_batch = false;
@@ -1090,6 +1093,29 @@ rmc_status grow_queue(rmc_ctx *c, unsigned long long max_region) {
   return layout_queue(c, c->pq_regions);
 }
 
+// Waves (2^lp packets each) that the walkers' launches run `live` packets of
+// n_probs problems on; 0: too many for one wave per SIMD (or, with many
+// problems, for each problem to have waves of its own).  Up to eight packets a
+// wave, one wave per CU is faster than fewer packets on more waves, which
+// share the CUs' instruction caches: cycles per event (float slab / float
+// sphere with peel-off) at 1024 packets 4180 / 4444 on 256 waves against
+// 4834 / 4854 on 512 and 6564 / 5839 on 1024; at 4096 packets (16 a wave on
+// 256) 5287 / 5920 against 5628 / 4803 on 1024, and beyond that the more waves
+// the faster.  k_transport took 7118 / 9122 at 1024 packets.
+int walker_waves(const rmc_ctx *c, int64_t live, int n_probs, int *lp) {
+  const int64_t extra = std::min<int64_t>(n_probs - 1, live);   // each problem's last wave may be partly filled
+  for (const int64_t most : {(int64_t)c->num_cus, (int64_t)c->num_cus * 4}) {
+    for (int l = 0; l <= (most == c->num_cus ? 3 : 6); ++l) {
+      const int64_t w = ((live + (1 << l) - 1) >> l) + extra;
+      if (w <= most) {
+        *lp = l;
+        return (int)w;
+      }
+    }
+  }
+  return 0;
+}
+
 // Prepare slots and counters for a stream over the problems already
 // uploaded at s_probs / s_starts.
 rmc_status stream_open(rmc_ctx *c, int64_t total, int n_probs, int levels, bool batch) {
@@ -1100,21 +1126,36 @@ rmc_status stream_open(rmc_ctx *c, int64_t total, int n_probs, int levels, bool 
   c->s_levels = std::max(levels, 1);
   c->s_batch = batch;
   c->s_grid = grid_for(c, total, batch, levels);
-  c->s_tail_grid = 0;
+  c->s_tail_grid = c->s_walk_waves = 0;
   const int64_t n_slots = (int64_t)c->s_grid * c->block;
   HIPCHK(c, c->slots.ensure((size_t)n_slots * slot_bytes()));
   HIPCHK(c, c->d_slice.ensure((N_STATS + 4) * 8));
   const int n_waves = (int)(n_slots / 64);
   HIPCHK(c, c->d_next.ensure((RESERVE_OFFSET + 2 * (size_t)n_waves) * 8));
+  c->s_slots = c->slots.p;
   HIPCHK(c, launch_clear_slots(c->slots.p, n_slots, c->stream));
   if (c->s_pq) {
-    rmc_status r = layout_queue(c, (unsigned long long)n_slots / 64);
+    // a region per wave of the full grid, or of the walkers' launches later on
+    // (of both where they share the first launch)
+    int lp = 0;
+    const int64_t walkers = c->compact ? std::min<int64_t>((int64_t)c->num_cus * 4, 2 * total) : 0;
+    const bool both = walker_waves(c, total, n_probs, &lp) > 0;
+    rmc_status r = layout_queue(c, (unsigned long long)(both ? n_waves + walkers : std::max<int64_t>(n_waves, walkers)));
     if (r) return r;
   }
   HIPCHK(c, launch_batch_reset(c->s_probs, n_probs, c->d_next.as<unsigned long long>(), n_waves,
                                c->stream));
   std::memset(&c->s_acc, 0, sizeof c->s_acc);
   c->s_open = true;
+  return RMC_OK;
+}
+
+// The captured launches of a step of the open stream (built at the first
+// step that needs them: a run of few packets goes to the walkers at once).
+rmc_status stream_graphs(rmc_ctx *c) {
+  const int n_probs = c->s_nprobs;
+  const bool batch = c->s_batch;
+  const int64_t n_slots = (int64_t)c->s_grid * c->block;
   // one slice = zero the slice counters, one transport launch; captured
   // once per shape and replayed
   char key[256];
@@ -1165,28 +1206,50 @@ rmc_status stream_open(rmc_ctx *c, int64_t total, int n_probs, int levels, bool 
   return RMC_OK;
 }
 
+// Gather the live packets (at most `live`) of the first `lanes` slots to the
+// front of the other slot array, for the walkers' launches (waves of 2^lp) or,
+// with waves 0, for the transport; *d_live becomes their count.
+rmc_status gather_slots(rmc_ctx *c, int64_t live, int64_t lanes, int waves, int lp) {
+  const int new_grid = (int)((live + c->block - 1) / c->block);
+  const int64_t n_new = waves > 0 ? (int64_t)waves << lp : (int64_t)new_grid * c->block;
+  DevBuf &dst = c->s_slots == c->slots2.p ? c->slots : c->slots2;
+  HIPCHK(c, dst.ensure((size_t)n_new * slot_bytes()));
+  const int64_t n_work = 1 + (c->s_batch ? (c->s_nprobs + 1) / 2 : 0);   // the live count, then 32 bits a problem
+  HIPCHK(c, c->d_live.ensure((size_t)n_work * 8));
+  unsigned long long *n_live = c->d_live.as<unsigned long long>();
+  HIPCHK(c, launch_clear_slots(dst.p, n_new, c->stream));
+  HIPCHK(c, launch_fill_u64(n_live, n_work, 0ull, c->stream));
+  if (waves > 0 && c->s_batch)
+    HIPCHK(c, launch_group_slots(c->s_slots, lanes, dst.p, n_new, c->s_nprobs, lp, (uint32_t *)(n_live + 1), n_live,
+                                 c->stream));
+  else
+    HIPCHK(c, launch_compact_slots(c->s_slots, lanes, dst.p, n_live, c->stream));
+  c->s_slots = dst.p;
+  c->s_walk_waves = waves;
+  c->s_walk_lp = lp;
+  c->s_tail_grid = waves > 0 ? 0 : new_grid;
+  return RMC_OK;
+}
+
 // Once every packet of the stream has started (the queue is drained), the
 // live packets are total - done, all parked in slots.  When they fill at
-// most three quarters of the lanes launched, gather them to the front
-// (through slots2) and run the next launches with the blocks they fill:
-// the last, longest walks then share the SIMDs with fewer waves, and each
-// wave issues its instructions faster.  Which lane runs a packet does not
+// most three quarters of the lanes launched (or always, with force), gather
+// them to the front of the other slot array.  As soon as they fit one wave per
+// SIMD the next launches are the walkers'; before, the transport with the
+// blocks they fill: the longer walks then share the SIMDs with fewer waves, and
+// each wave issues its instructions faster.  Which lane runs a packet does not
 // change its walk, so results are those of the full grid (cube additions
 // aside, whose order differs).
 rmc_status gather_tail(rmc_ctx *c) {
   const int64_t live = c->s_total - c->s_done;
-  const int grid = c->s_tail_grid > 0 ? c->s_tail_grid : c->s_grid;
-  const int64_t lanes = (int64_t)grid * c->block;
-  if (live > lanes * 3 / 4) return RMC_OK;
-  const int new_grid = (int)((live + c->block - 1) / c->block);
-  const int64_t n_new = (int64_t)new_grid * c->block;
-  HIPCHK(c, c->slots2.ensure((size_t)n_new * slot_bytes()));
-  HIPCHK(c, c->d_live.ensure(8));
-  HIPCHK(c, launch_clear_slots(c->slots2.p, n_new, c->stream));
-  HIPCHK(c, launch_fill_u64(c->d_live.as<unsigned long long>(), 1, 0ull, c->stream));
-  HIPCHK(c, launch_compact_slots(c->slots.p, lanes, c->slots2.p, c->d_live.as<unsigned long long>(), c->stream));
-  HIPCHK(c, hipMemcpyAsync(c->slots.p, c->slots2.p, (size_t)n_new * slot_bytes(), hipMemcpyDeviceToDevice,
-                           c->stream));
+  const int64_t lanes = c->s_walk_waves > 0 ? (int64_t)c->s_walk_waves << c->s_walk_lp
+                                            : (int64_t)(c->s_tail_grid > 0 ? c->s_tail_grid : c->s_grid) * c->block;
+  if (live <= 0 || live > lanes * 3 / 4) return RMC_OK;
+  int lp = 0;
+  const int waves = c->s_defer ? walker_waves(c, live, c->s_nprobs, &lp) : 0;
+  if (c->s_walk_waves > 0 && lp == c->s_walk_lp && waves * 4 > c->s_walk_waves * 3) return RMC_OK;
+  rmc_status r = gather_slots(c, live, lanes, waves, lp);
+  if (r) return r;
   unsigned long long got = 0;
   HIPCHK(c, hipMemcpyAsync(&got, c->d_live.p, 8, hipMemcpyDeviceToHost, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
@@ -1194,7 +1257,76 @@ rmc_status gather_tail(rmc_ctx *c) {
     c->s_open = false;
     return fail(c, RMC_EDEVICE, "gathering the last packets: %llu parked, %lld expected", got, (long long)live);
   }
-  c->s_tail_grid = new_grid;
+  return RMC_OK;
+}
+
+// One launch of the open stream of at most `budget` loop iterations per lane
+// (in the walkers' and the gathered launches; the captured one runs
+// slice_iters), its ray-cast pass and its counters, added to z.  start_walkers:
+// the stream's first launch, of so few packets that one loop iteration starts
+// them all and the walkers take over in the same step, with no word to the
+// host in between (their waves are those that all packets would need).
+rmc_status stream_launch(rmc_ctx *c, int budget, bool start_walkers, rmc_run_stats *z) {
+  const bool f32 = c->precision == RMC_FP32_BULK;
+  unsigned long long *d_slice = c->d_slice.as<unsigned long long>();
+  int regions = 0;   // of the peel-off queue that the launch fills
+  if (c->s_walk_waves == 0 && c->s_tail_grid == 0 && !start_walkers) {
+    rmc_status r = stream_graphs(c);
+    if (r) return r;
+    HIPCHK(c, hipEventRecord(c->ev0, c->stream));
+    HIPCHK(c, hipGraphLaunch(c->s_graph, c->stream));
+    HIPCHK(c, hipEventRecord(c->ev1, c->stream));
+    if (c->s_pq) HIPCHK(c, hipGraphLaunch(c->s_graph2, c->stream));
+  } else {
+    // the captured launches with the shape of the gathered slots
+    const int tg = c->s_tail_grid > 0 ? c->s_tail_grid : c->s_grid;
+    HIPCHK(c, hipEventRecord(c->ev0, c->stream));
+    HIPCHK(c, launch_fill_u64(d_slice, N_STATS + 4, 0ull, c->stream));
+    if (c->s_walk_waves == 0) {
+      HIPCHK(c, launch_transport(f32, c->s_batch, c->s_defer, c->s_one_line, c->regroup != 0, c->s_probs, c->s_starts,
+                                 c->s_nprobs, c->d_next.as<unsigned long long>(), c->refill, c->s_levels, tg, c->block,
+                                 c->s_slots, start_walkers ? 1 : budget, d_slice, c->stream));
+      regions = tg * (c->block / 64);
+      if (start_walkers) {
+        int lp = 0;
+        const int waves = walker_waves(c, c->s_total, c->s_nprobs, &lp);
+        rmc_status r = gather_slots(c, c->s_total, (int64_t)tg * c->block, waves, lp);
+        if (r) return r;
+        --budget;
+      }
+    }
+    if (c->s_walk_waves > 0) {
+      HIPCHK(c, launch_walkers(f32, c->s_batch, c->s_one_line, c->s_probs, regions, c->s_levels, c->s_slots,
+                               c->s_walk_lp, c->s_walk_waves, budget, d_slice, c->stream));
+      regions += c->s_walk_waves;
+    }
+    HIPCHK(c, hipEventRecord(c->ev1, c->stream));
+    if (c->s_pq)
+      HIPCHK(c, launch_peel_drain(f32, c->s_batch, c->s_one_line, c->s_probs, c->s_pq, regions, c->s_levels,
+                                  c->num_cus * peel_drain_blocks_per_cu(f32, c->s_batch, c->s_one_line, c->s_levels),
+                                  d_slice, c->stream));
+  }
+  HIPCHK(c, hipEventRecord(c->ev2, c->stream));
+  unsigned long long h[N_STATS + 4];
+  HIPCHK(c, hipMemcpyAsync(h, d_slice, sizeof h, hipMemcpyDeviceToHost, c->stream));
+  HIPCHK(c, hipStreamSynchronize(c->stream));
+  float ms = 0.f, ms2 = 0.f;
+  HIPCHK(c, hipEventElapsedTime(&ms, c->ev0, c->ev1));
+  HIPCHK(c, hipEventElapsedTime(&ms2, c->ev1, c->ev2));
+  fill_stats(z, h, ms);
+  z->peel_deferred = h[N_STATS];
+  z->peel_pass_ms = c->s_pq ? ms2 : 0.0;
+  if (c->s_pq) {
+    if (h[N_STATS + 2]) {
+      c->s_open = false;
+      return fail(c, RMC_EDEVICE, "peel-off queue: %llu rays found their region full", h[N_STATS + 2]);
+    }
+    z->slices_cut = slice_cut(c, h[N_STATS + 1]) ? 1 : 0;
+    rmc_status r = grow_queue(c, h[N_STATS + 1]);
+    if (r) return r;
+  }
+  c->s_done += (int64_t)h[S_EMITTED];
+  c->s_started += (int64_t)h[N_STATS + 3];
   return RMC_OK;
 }
 
@@ -1207,57 +1339,16 @@ rmc_status stream_step(rmc_ctx *c, rmc_run_stats *slice, int64_t *remaining) {
     if (remaining) *remaining = 0;
     return RMC_OK;
   }
-  HIPCHK(c, hipEventRecord(c->ev0, c->stream));
-  if (c->s_tail_grid > 0) {
-    // the captured launches with the grid of the gathered slots
-    const bool f32 = c->precision == RMC_FP32_BULK;
-    HIPCHK(c, launch_fill_u64(c->d_slice.as<unsigned long long>(), N_STATS + 4, 0ull, c->stream));
-    // at most one wave per SIMD: the kernel compiled for one (no spills)
-    const bool lone = (int64_t)c->s_tail_grid * (c->block / 64) <= (int64_t)c->num_cus * 4;
-    HIPCHK(c, launch_transport(f32, c->s_batch, c->s_defer, c->s_one_line, c->regroup != 0, c->s_probs,
-                               c->s_starts, c->s_nprobs, c->d_next.as<unsigned long long>(), c->refill,
-                               c->s_levels, c->s_tail_grid, c->block, c->slots.p, c->slice_iters,
-                               c->d_slice.as<unsigned long long>(), c->stream, lone));
-    HIPCHK(c, hipEventRecord(c->ev1, c->stream));
-    if (c->s_pq) {
-      const int grid = c->num_cus * peel_drain_blocks_per_cu(f32, c->s_batch, c->s_one_line, c->s_levels);
-      HIPCHK(c, launch_peel_drain(f32, c->s_batch, c->s_one_line, c->s_probs, c->s_pq,
-                                  c->s_tail_grid * (c->block / 64), c->s_levels, grid,
-                                  c->d_slice.as<unsigned long long>(), c->stream));
-    }
-  } else {
-    HIPCHK(c, hipGraphLaunch(c->s_graph, c->stream));
-    HIPCHK(c, hipEventRecord(c->ev1, c->stream));
-    if (c->s_pq) HIPCHK(c, hipGraphLaunch(c->s_graph2, c->stream));
-  }
-  HIPCHK(c, hipEventRecord(c->ev2, c->stream));
-  unsigned long long h[N_STATS + 4];
-  HIPCHK(c, hipMemcpyAsync(h, c->d_slice.p, sizeof h, hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));
-  float ms = 0.f, ms2 = 0.f;
-  HIPCHK(c, hipEventElapsedTime(&ms, c->ev0, c->ev1));
-  HIPCHK(c, hipEventElapsedTime(&ms2, c->ev1, c->ev2));
-  fill_stats(&z, h, ms);
-  z.peel_deferred = h[N_STATS];
-  z.peel_pass_ms = c->s_pq ? ms2 : 0.0;
-  if (c->s_pq) {
-    if (h[N_STATS + 2]) {
-      c->s_open = false;
-      return fail(c, RMC_EDEVICE, "peel-off queue: %llu rays found their region full", h[N_STATS + 2]);
-    }
-    z.slices_cut = slice_cut(c, h[N_STATS + 1]) ? 1 : 0;
-    rmc_status r = grow_queue(c, h[N_STATS + 1]);
-    if (r) return r;
-  }
-  c->s_done += (int64_t)h[S_EMITTED];
-  c->s_started += (int64_t)h[N_STATS + 3];
+  int lp;
+  const bool start_walkers = c->s_started == 0 && c->compact && c->s_defer && c->slice_iters > 1 &&
+                             (int64_t)c->s_grid * c->block >= c->s_total &&
+                             walker_waves(c, c->s_total, c->s_nprobs, &lp) > 0;
+  rmc_status r = stream_launch(c, c->slice_iters, start_walkers, &z);
+  if (r) return r;
   add_run_stats(c->s_acc, z);
   if (slice) *slice = z;
   if (remaining) *remaining = c->s_total - c->s_done;
-  if (c->compact && c->s_started >= c->s_total && c->s_done < c->s_total) {
-    rmc_status r = gather_tail(c);
-    if (r) return r;
-  }
+  if (c->compact && c->s_started >= c->s_total && c->s_done < c->s_total) return gather_tail(c);
   return RMC_OK;
 }
 

@@ -106,7 +106,7 @@ struct PeelQueue {
   uint32_t *offs;                 // [n_regions + 1]: jobs queued in the regions before each one
   unsigned long long cap;         // jobs per region (a wave stops its slice before it)
   unsigned long long n_regions;   // regions of the last launch's waves (set by k_peel_scan)
-  unsigned long long take;        // jobs handed out by the ray-cast pass
+  unsigned long long take;        // jobs handed out by the ray-cast pass (beyond each wave's first run)
   unsigned long long lost;        // pushes that found their region full (an error)
 };
 
@@ -552,6 +552,24 @@ __device__ __forceinline__ bool upar_try_pair(const UparEnv<float> &e, float a, 
   return r3 < M<float>::exp(lim - u * u);
 }
 
+// One double round from its three draws: r1 picks the piece, r2 the angle
+// within it, r3 accepts or rejects.
+__device__ __forceinline__ bool upar_try_triple(const UparEnv<double> &e, double a, double r1, double r2, double r3,
+                                                double *out) {
+  const double hp = 0.5 * PI_D;
+  double th, lim;
+  if (r1 < e.p1) {
+    th = -hp + r2 * (e.th0 + hp);
+    lim = 0.0;
+  } else {
+    th = e.th0 + r2 * (hp - e.th0);
+    lim = e.u02;
+  }
+  const double u = e.xa + a * M<double>::tan(th);
+  *out = e.sg * u;
+  return r3 < M<double>::exp(lim - u * u);
+}
+
 // Round `it` of the rejection draw (|x| < 8): true when it accepts, with
 // the velocity in *out.
 template <class R>
@@ -561,29 +579,23 @@ __device__ __forceinline__ bool upar_try(const UparEnv<R> &e, R a, EventRng<R> &
     rng.round(it, &r1, &r3);
     return upar_try_pair(e, a, r1, r3, out);
   } else {
-    const R hp = R(0.5 * PI_D);
-    R th, lim;
     const R r1 = rng.u(J_REJ + 3 * it);
     const R r2 = rng.u(J_REJ + 3 * it + 1);
     const R r3 = rng.u(J_REJ + 3 * it + 2);
-    if (r1 < e.p1) {
-      th = -hp + r2 * (e.th0 + hp);
-      lim = R(0);
-    } else {
-      th = e.th0 + r2 * (hp - e.th0);
-      lim = e.u02;
-    }
-    const R u = e.xa + a * M<R>::tan(th);
-    *out = e.sg * u;
-    return r3 < M<R>::exp(lim - u * u);
+    return upar_try_triple(e, a, r1, r2, r3, out);
   }
 }
 
-// The |x| >= 8 branch: Gaussian of variance 1/2 centred at 1/x.
-template <class R> __device__ __forceinline__ R upar_gauss(R x, EventRng<R> &rng) {
+// The |x| >= 8 branch: Gaussian of variance 1/2 centred at 1/x, from its
+// Box-Muller pair (draws J_GAUSS1, J_GAUSS2).
+template <class R> __device__ __forceinline__ R upar_gauss(R x, R g1, R g2) {
   R s, c;
-  M<R>::sincos2pi(rng.u(J_GAUSS2), &s, &c);
-  return M<R>::div(R(1), x) + M<R>::sqrt(-M<R>::log(rng.u(J_GAUSS1))) * c;
+  M<R>::sincos2pi(g2, &s, &c);
+  return M<R>::div(R(1), x) + M<R>::sqrt(-M<R>::log(g1)) * c;
+}
+template <class R> __device__ __forceinline__ R upar_gauss(R x, EventRng<R> &rng) {
+  const R g2 = rng.u(J_GAUSS2);
+  return upar_gauss<R>(x, rng.u(J_GAUSS1), g2);
 }
 #pragma clang fp contract(fast)
 

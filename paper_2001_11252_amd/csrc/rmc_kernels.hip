@@ -7,6 +7,8 @@
 //               (ballot + mbcnt ranks of the idle lanes).  Each
 //               peel-off ray is decided in the scattering's own leaf or
 //               queued in the wave's region of the peel-off queue.
+// k_walkers     the transport of a run's last packets: a few packets a wave,
+//               their draws and peel-off computed by all its lanes
 // k_peel_drain  ray-cast pass over the queued peel-off rays after each
 //               transport launch (lanes refilled per ray), k_peel_scan
 //               the index of its jobs
@@ -531,33 +533,99 @@ __device__ void emit(const ProblemK &pb, int64_t pid, Lane<R> &s, int *stk, int 
   }
 }
 
+// Sums of products with the fused ones named, so that every kernel that
+// inlines them rounds alike (the walkers' kernel gets the sines and cosines
+// from elsewhere than the bulk kernels, and the compiler would pick other
+// products to fuse).
+__device__ __forceinline__ float fmadd(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fmadd(double a, double b, double c) { return __builtin_fma(a, b, c); }
+// a b + c d with c d rounded first
+template <class R> __device__ __forceinline__ R dot2(R a, R b, R c, R d) {
+  const R t = c * d;
+  return fmadd(a, b, t);
+}
+// (a0 b0 + a1 b1) + a2 b2 with a1 b1 rounded first
+template <class R> __device__ __forceinline__ R dot3(R a0, R b0, R a1, R b1, R a2, R b2) {
+  return fmadd(a2, b2, dot2(a0, b0, a1, b1));
+}
+// The direction at angle cosine mu (sine st) from kin and azimuth (sp, cp)
+// in the plane of e1, e2.
+template <class R>
+__device__ __forceinline__ void rotate(R k[3], R mu, R st, R sp, R cp, const R kin[3], const R e1[3], const R e2[3]) {
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const R t = sizeof(R) == 4 ? dot2(cp, e1[d], sp, e2[d]) : dot2(sp, e2[d], cp, e1[d]);
+    k[d] = dot2(mu, kin[d], st, t);
+  }
+}
+
+// The draws of one event in the order the interaction takes them, computed
+// where they are used (bulk kernels).
+template <class R, bool REGROUP> struct RngDraws {
+  EventRng<R> rng;
+  R r_late, r_mu, r_p1, r_p2, r_phi;
+  __device__ __forceinline__ RngDraws(const ProblemK &pb, const Lane<R> &s) : rng(pb.seed, (uint64_t)s.pid, s.event) {}
+  // kappa_d / kappa reaches ~1e-8 in optically thick line cores
+  __device__ __forceinline__ R channel() {
+    const R r = rng.u_small(J_CHANNEL);
+    // the double generator keeps one Philox block: the draw of the channel's
+    // block that the event uses last (the scattering angle) is taken now, so
+    // that no block of the event is computed twice; the float path takes the
+    // draws of block 0 it needs late now (tau_event and the scattering angle),
+    // which leaves that block's words dead after the first rejection round
+    r_late = rng.u(sizeof(R) == 4 ? J_TAU : J_MU);
+    if constexpr (sizeof(R) == 4) r_mu = rng.u(J_MU);
+    return r;
+  }
+  __device__ __forceinline__ R albedo() { return rng.u(J_ALBEDO); }
+  __device__ __forceinline__ R mu() { return sizeof(R) == 8 ? r_late : r_mu; }
+  __device__ __forceinline__ R log_tau() { return M<R>::log(sizeof(R) == 4 ? r_late : rng.u(J_TAU)); }
+  // float: block 1 (the second rejection round, the perpendicular
+  // velocities and the azimuth) for every lane of the line branch at once, its
+  // outgoing draws taken now so that its words are dead after the
+  // sampler's second round
+  __device__ __forceinline__ void line() {
+    if constexpr (sizeof(R) == 4) {
+      rng.need1();
+      r_p1 = rng.u(J_PERP1);
+      r_p2 = rng.u(J_PERP2);
+      r_phi = rng.u(J_PHI);
+    }
+  }
+  __device__ __forceinline__ R log_perp() { return M<R>::log(sizeof(R) == 4 ? r_p1 : rng.u(J_PERP1)); }
+  __device__ __forceinline__ void perp(R *sp, R *cp) { M<R>::sincos2pi(sizeof(R) == 4 ? r_p2 : rng.u(J_PERP2), sp, cp); }
+  __device__ __forceinline__ void phi(R *sp, R *cp) { M<R>::sincos2pi(sizeof(R) == 4 ? r_phi : rng.u(J_PHI), sp, cp); }
+  // (the dust branch has not taken block 1)
+  __device__ __forceinline__ void phi_dust(R *sp, R *cp) { M<R>::sincos2pi(rng.u(J_PHI), sp, cp); }
+  __device__ __forceinline__ R decay() { return rng.u(J_DECAY); }
+  __device__ __forceinline__ R dipole(bool core) { return mu_dipole(mu(), core); }
+  // The parallel atom velocity: false when the rounds run out, or (regrouped
+  // draw) when this call's round is rejected; then undrawn() is the packet's
+  // status (a pending event's packet lives on, with s.rej rounds run).
+  __device__ __forceinline__ bool upar(Lane<R> &s, R x, R a, R la, R *out) {
+    if constexpr (REGROUP) {
+      if (!upar_round<R>(x, a, la, rng, s.rej, out)) return false;
+      s.rej = 0;
+      return true;
+    } else {
+      return sample_upar<R>(x, a, la, rng, out);
+    }
+  }
+  static __device__ __forceinline__ int undrawn(Lane<R> &s) {
+    return REGROUP && ++s.rej < MAX_REJECT ? ST_NONE : ST_STUCK;
+  }
+};
+
 // Interaction at the current position (Sect. 3.2).  Returns the packet's
-// status (ST_NONE while it lives).
+// status (ST_NONE while it lives).  dr gives the event's draws, peel(ps)
+// takes what its peel-off needs.
 // With REGROUP a line scattering runs one rejection round of its u_par
 // draw per call: a rejected round leaves the event pending (s.rej rounds
 // run) and the packet where it is, and the next pass of the transport loop
 // calls again for the next round (the same draws as the looping sampler).
-template <class R, bool DEFER, int NL, bool REGROUP = false>
-__device__ int interact(const ProblemK &pb, Lane<R> &s, const Opac<R, NL> &o, int *pstk, const int *stk,
-                        const PeelSink<R> &snk, int stride) {
-  const StartCell<R> sc{&s.c, &s.lf, stk};
-  if (!REGROUP || s.rej == 0) {
-    ++s.event;
-    if (pb.max_events > 0 && (int64_t)s.event >= pb.max_events) return ST_STUCK;
-  }
-  EventRng<R> rng(pb.seed, (uint64_t)s.pid, s.event);
-  // kappa_d / kappa reaches ~1e-8 in optically thick line cores
-  R r = rng.u_small(J_CHANNEL) * o.ktot;
-  // the double generator keeps one Philox block: the draw of the channel's
-  // block that the event uses last (the scattering angle) is taken now, so
-  // that no block of the event is computed twice; the float path takes the
-  // draws of block 0 it needs late now (tau_event and the scattering angle),
-  // which leaves that block's words dead after the first rejection round
-  const R r_late = rng.u(sizeof(R) == 4 ? J_TAU : J_MU);
-  R r_mu = R(0);
-  if constexpr (sizeof(R) == 4) r_mu = rng.u(J_MU);
-  auto u_mu = [&]() { return sizeof(R) == 8 ? r_late : r_mu; };
-  auto u_tau = [&]() { return sizeof(R) == 4 ? r_late : rng.u(J_TAU); };
+template <class R, int NL, class D, class P>
+__device__ __forceinline__ int interact(const ProblemK &pb, Lane<R> &s, const Opac<R, NL> &o, D &dr, P &&peel) {
+  R r = dr.channel() * o.ktot;
   const R kin[3] = {s.k[0], s.k[1], s.k[2]};
   // the pair perpendicular to k_in is formed where it is used (after the
   // atom-velocity draw on the line branch, whose register peak it would
@@ -569,21 +637,20 @@ __device__ int interact(const ProblemK &pb, Lane<R> &s, const Opac<R, NL> &o, in
   ps.w = o.w;
   if (r < o.kd) {
     // dust (Sect. 3.2.2): absorbed with probability 1 - albedo, else HG
-    if (rng.u(J_ALBEDO) >= cst<R>(pb.albedo, pb.albedo_f)) return ST_ABSORBED;
+    if (dr.albedo() >= cst<R>(pb.albedo, pb.albedo_f)) return ST_ABSORBED;
     ++s.cnt.dust_scat;
     if (pb.n_obs) {
       ps.kind = 2;
       ps.x = s.x;
-      peel_all<R, DEFER, NL>(pb, s.p, ps, pstk, stride, s.cnt, snk, &sc);
+      peel(ps);
     }
     if (!pb.forward_only) {
       perp_basis(kin, e1, e2);
-      const R mu = mu_hg(u_mu(), cst<R>(pb.g_hg, pb.g_hg_f));
+      const R mu = mu_hg(dr.mu(), cst<R>(pb.g_hg, pb.g_hg_f));
       R sp, cp;
-      M<R>::sincos2pi(rng.u(J_PHI), &sp, &cp);
+      dr.phi_dust(&sp, &cp);
       const R st = M<R>::sqrt(fmax(R(0), R(1) - mu * mu));
-#pragma unroll
-      for (int d = 0; d < 3; ++d) s.k[d] = mu * kin[d] + st * (cp * e1[d] + sp * e2[d]);
+      rotate(s.k, mu, st, sp, cp, kin, e1, e2);
       set_geom_dir(s);
       // coherent in the cell frame
       const R wn = s.k[0] * s.lf.ux + s.k[1] * s.lf.uy + s.k[2] * s.lf.uz;
@@ -615,41 +682,20 @@ __device__ int interact(const ProblemK &pb, Lane<R> &s, const Opac<R, NL> &o, in
     // log10 a for the envelope: the double path adds the line's log10 alpha
     // and the leaf's log10(1/rho) (its record holds it)
     const R la = sizeof(R) == 8 ? R(ln.lalpha) + s.lf.lg : M<R>::log10(a);
-    // float: block 1 (the second rejection round, the perpendicular
-    // velocities and the azimuth) for every lane of the branch at once, its
-    // outgoing draws taken now so that its words are dead after the
-    // sampler's second round
-    R r_p1 = R(0), r_p2 = R(0), r_phi = R(0);
-    if constexpr (sizeof(R) == 4) {
-      rng.need1();
-      r_p1 = rng.u(J_PERP1);
-      r_p2 = rng.u(J_PERP2);
-      r_phi = rng.u(J_PHI);
-    }
-    auto u_p1 = [&]() { return sizeof(R) == 4 ? r_p1 : rng.u(J_PERP1); };
-    auto u_p2 = [&]() { return sizeof(R) == 4 ? r_p2 : rng.u(J_PERP2); };
-    auto u_phi = [&]() { return sizeof(R) == 4 ? r_phi : rng.u(J_PHI); };
+    dr.line();
     R upar;
-    if constexpr (REGROUP) {
-      if (!upar_round<R>(x, a, la, rng, s.rej, &upar)) {
-        if (++s.rej >= MAX_REJECT) return ST_STUCK;
-        return ST_NONE;
-      }
-      s.rej = 0;
-    } else {
-      if (!sample_upar<R>(x, a, la, rng, &upar)) return ST_STUCK;
-    }
+    if (!dr.upar(s, x, a, la, &upar)) return dr.undrawn(s);
     // Gaussian u_perp (Box-Muller), restricted to |u_perp| >= x_crit while
     // core-skipping applies
     const R xc2 = pb.skip_tau > 0.0 ? core_skip_x2<R>(pb, ln, s.lf, s.c.level, a, x) : R(0);
     perp_basis(kin, e1, e2);
     R sp, cp;
-    M<R>::sincos2pi(u_p2(), &sp, &cp);
-    const R rr = M<R>::sqrt(xc2 - M<R>::log(u_p1()));
+    dr.perp(&sp, &cp);
+    const R rr = M<R>::sqrt(xc2 - dr.log_perp());
     const R up1 = rr * cp, up2 = rr * sp;
     R U[3];
 #pragma unroll
-    for (int d = 0; d < 3; ++d) U[d] = upar * kin[d] + up1 * e1[d] + up2 * e2[d];
+    for (int d = 0; d < 3; ++d) U[d] = fmadd(up2, e2[d], dot2(upar, kin[d], up1, e1[d]));
     const R rho = M<R>::div(R(1), s.lf.irho);
     const R bc = cst<R>(pb.b_ref, pb.b_ref_f) * cst<R>(ln.mu, ln.f.mu) * rho;
     // frequency seen by the atom, nu_in (1 - k_in.v/c), within 0.2 dnu_D
@@ -661,7 +707,7 @@ __device__ int interact(const ProblemK &pb, Lane<R> &s, const Opac<R, NL> &o, in
     int fch = -1;
     if constexpr (NL > 1) {
       if (ln.n_fluor > 0 && !pb.forward_only) {
-        const R ud = rng.u(J_DECAY);
+        const R ud = dr.decay();
         if (ud >= cst<R>(ln.a_res, ln.f.a_res)) fch = (ln.n_fluor > 1 && ud >= cst<R>(ln.a_cum0, ln.f.a_cum0)) ? 1 : 0;
       }
     }
@@ -673,18 +719,19 @@ __device__ int interact(const ProblemK &pb, Lane<R> &s, const Opac<R, NL> &o, in
         ps.bc = bc;
         ps.line = i;
         ps.core = fch;
-        peel_all<R, DEFER, NL>(pb, s.p, ps, pstk, stride, s.cnt, snk, &sc);
+        peel(ps);
       }
-      const R mu = R(2) * u_mu() - R(1);
-      M<R>::sincos2pi(u_phi(), &sp, &cp);
+      const R mu = R(2) * dr.mu() - R(1);
+      dr.phi(&sp, &cp);
       const R st = M<R>::sqrt(fmax(R(0), R(1) - mu * mu));
-#pragma unroll
-      for (int d = 0; d < 3; ++d) s.k[d] = mu * kin[d] + st * (cp * e1[d] + sp * e2[d]);
+      rotate(s.k, mu, st, sp, cp, kin, e1, e2);
       set_geom_dir(s);
-      const R ba = bc * (s.k[0] * U[0] + s.k[1] * U[1] + s.k[2] * U[2]);
-      const R bw = cst<R>(pb.b_ref, pb.b_ref_f) * (s.k[0] * s.lf.ux + s.k[1] * s.lf.uy + s.k[2] * s.lf.uz);
-      s.x = cst<R>(ln.xf0[fch], ln.f.xf0[fch]) + M<R>::div(cst<R>(ln.sf[fch], ln.f.sf[fch]) * (ba + bw + ba * bw), cst<R>(pb.b_ref, pb.b_ref_f));
-      s.tau = -(double)M<R>::log(u_tau());
+      const R ku = dot3(s.k[0], U[0], s.k[1], U[1], s.k[2], U[2]);
+      const R bw = cst<R>(pb.b_ref, pb.b_ref_f) * dot3(s.k[0], s.lf.ux, s.k[1], s.lf.uy, s.k[2], s.lf.uz);
+      const R ba = bc * ku;
+      const R shift = fmadd(ba, bw, fmadd(bc, ku, bw));   // ba + bw + ba bw
+      s.x = cst<R>(ln.xf0[fch], ln.f.xf0[fch]) + M<R>::div(cst<R>(ln.sf[fch], ln.f.sf[fch]) * shift, cst<R>(pb.b_ref, pb.b_ref_f));
+      s.tau = -(double)dr.log_tau();
       return ST_NONE;
     }
     if (pb.n_obs) {
@@ -696,19 +743,17 @@ __device__ int interact(const ProblemK &pb, Lane<R> &s, const Opac<R, NL> &o, in
       ps.irho = s.lf.irho;
       ps.line = i;
       ps.core = core;
-      peel_all<R, DEFER, NL>(pb, s.p, ps, pstk, stride, s.cnt, snk, &sc);
+      peel(ps);
     }
     if (!pb.forward_only) {
-      const R ru = u_mu();
-      const R mu = ln.phase == PHASE_ISO ? R(2) * ru - R(1) : mu_dipole(ru, core != 0);
-      M<R>::sincos2pi(u_phi(), &sp, &cp);
+      const R mu = ln.phase == PHASE_ISO ? R(2) * dr.mu() - R(1) : dr.dipole(core != 0);
+      dr.phi(&sp, &cp);
       const R st = M<R>::sqrt(fmax(R(0), R(1) - mu * mu));
-#pragma unroll
-      for (int d = 0; d < 3; ++d) s.k[d] = mu * kin[d] + st * (cp * e1[d] + sp * e2[d]);
+      rotate(s.k, mu, st, sp, cp, kin, e1, e2);
       set_geom_dir(s);
       // outgoing frequency, coherent in the atom frame, recoil in the
       // denominator (Eq. for nu_out), then back to the external frame
-      const R dkU = (s.k[0] - kin[0]) * U[0] + (s.k[1] - kin[1]) * U[1] + (s.k[2] - kin[2]) * U[2];
+      const R dkU = dot3(s.k[0] - kin[0], U[0], s.k[1] - kin[1], U[1], s.k[2] - kin[2], U[2]);
       const R Rr = ln.recoil ? (R(1) - mu) * cst<R>(ln.rec, ln.f.rec) * g1 : R(0);
       R xc;
       if constexpr (sizeof(R) == 4) {
@@ -721,7 +766,7 @@ __device__ int interact(const ProblemK &pb, Lane<R> &s, const Opac<R, NL> &o, in
       s.x = (-cst<R>(ln.delta, ln.f.delta) + cst<R>(ln.mu, ln.f.mu) * rho * xc * (R(1) + cst<R>(pb.b_ref, pb.b_ref_f) * wn) + wn) * cst<R>(ln.inv_s, ln.f.inv_s);
     }
   }
-  s.tau = -(double)M<R>::log(u_tau());
+  s.tau = -(double)dr.log_tau();
   return ST_NONE;
 }
 
@@ -776,6 +821,40 @@ __device__ __forceinline__ void add_delta(SliceCount &a, const Lane<R> &s, const
   a.cross += s.cnt.cross - z.cnt.cross;
   a.peel_rays += s.cnt.peel_rays - z.cnt.peel_rays;
   a.peel_cross += s.cnt.peel_cross - z.cnt.peel_cross;
+}
+
+// A wave's counts of one launch into the launch's slice counters and, unless
+// null, a problem's totals: its lanes' work and the packets that ended
+// (ends[status - 1]).  Every lane calls it.
+__device__ __forceinline__ void publish(unsigned long long *stats, const SliceCount &acc, const int *ends,
+                                        unsigned long long *slice) {
+  const int lane = __lane_id();
+  if (lane == 0) {
+    unsigned long long n = 0;
+    for (int j = 0; j < 3; ++j) {
+      const unsigned long long e = (unsigned long long)(uint32_t)ends[j];
+      n += e;
+      if (e) {
+        atomicAdd(slice + S_ESCAPED + j, e);
+        if (stats) atomicAdd(stats + S_ESCAPED + j, e);
+      }
+    }
+    if (n) {
+      atomicAdd(slice + S_EMITTED, n);
+      if (stats) atomicAdd(stats + S_EMITTED, n);
+    }
+  }
+  const unsigned long long v[5] = {acc.scat, acc.dust, acc.cross, acc.peel_rays, acc.peel_cross};
+  const int idx[5] = {S_SCAT, S_DUST_SCAT, S_CROSS, S_PEEL_RAYS, S_PEEL_CROSS};
+#pragma unroll
+  for (int j = 0; j < 5; ++j) {
+    unsigned long long x = v[j];
+    for (int off = 32; off > 0; off >>= 1) x += __shfl_down(x, off);
+    if (lane == 0 && x) {
+      atomicAdd(slice + idx[j], x);
+      if (stats) atomicAdd(stats + idx[j], x);
+    }
+  }
 }
 
 // The first active lane's value, as a wave-uniform one.
@@ -833,15 +912,9 @@ template <bool BATCH, bool DEFER, int NL> struct WavesPerEU<double, BATCH, DEFER
 // takes its next round at the next pass of the loop, where it runs in step
 // with the other lanes' events (upar_round), instead of the wave looping
 // until its last lane accepts.
-// TAIL: the same kernel compiled for one wave per SIMD (registers to spare,
-// no spills), for the launches over gathered slots at the end of a run,
-// whose waves are no more than the SIMDs: each issues on its own, so its
-// latency, not the chip's throughput, sets the pace.  Every packet has
-// started by then: it holds no refill.
-template <class R, bool BATCH, bool DEFER, int NL, bool REGROUP = false, bool TAIL = false>
+template <class R, bool BATCH, bool DEFER, int NL, bool REGROUP = false>
 __global__ void __launch_bounds__(256)
-    __attribute__((amdgpu_waves_per_eu(TAIL ? 1 : WavesPerEU<R, BATCH, DEFER, NL>::v,
-                                       TAIL ? 1 : WavesPerEU<R, BATCH, DEFER, NL>::v)))
+    __attribute__((amdgpu_waves_per_eu(WavesPerEU<R, BATCH, DEFER, NL>::v, WavesPerEU<R, BATCH, DEFER, NL>::v)))
     k_transport(const ProblemK *__restrict__ probs,
                                                    const int64_t *__restrict__ starts, int n_probs,
                                                    unsigned long long *__restrict__ next,
@@ -908,9 +981,8 @@ __global__ void __launch_bounds__(256)
     const unsigned long long idle = __ballot(!active);
     const uint32_t n_idle = (uint32_t)__popcll(idle);
     const bool all_idle = n_idle == 64u;
-    if (TAIL && all_idle) break;   // every packet has started
-    if (!TAIL) debt += n_idle;
-    if (!TAIL && (all_idle || (!drained && debt >= REFILL_DEBT && (int)n_idle >= refill_min))) {
+    debt += n_idle;
+    if (all_idle || (!drained && debt >= REFILL_DEBT && (int)n_idle >= refill_min)) {
       debt = 0;
       if (fin != ST_NONE) {
         add_delta(acc, s, z);
@@ -1006,7 +1078,16 @@ __global__ void __launch_bounds__(256)
 #pragma unroll
       for (int d = 0; d < 3; ++d) s.p[d] = fmin(fmax(fma(dist, kd[d], s.p[d]), lo[d]), hi[d]);
       s.path += dist;
-      st = interact<R, DEFER, NL, REGROUP>(pb, s, o, pstk, stk, snk, stride);
+      if (!pend) ++s.event;
+        if (!pend && pb.max_events > 0 && (int64_t)s.event >= pb.max_events) {
+          st = ST_STUCK;
+        } else {
+          RngDraws<R, REGROUP> dr(pb, s);
+          const StartCell<R> sc{&s.c, &s.lf, stk};
+          st = interact<R, NL>(pb, s, o, dr, [&](const PeelSrc<R> &ps) {
+            peel_all<R, DEFER, NL>(pb, s.p, ps, pstk, stride, s.cnt, snk, &sc);
+          });
+        }
     } else {
       s.tau -= tseg;
       s.path += lmax;
@@ -1055,31 +1136,332 @@ __global__ void __launch_bounds__(256)
     reserve[0] = r_next;
     reserve[1] = r_end;
     if (started) atomicAdd(slice + N_STATS + 3, (unsigned long long)started);
-    unsigned long long n = 0;
-    for (int j = 1; j < 4; ++j) {
-      const unsigned long long e = (unsigned long long)(uint32_t)wcnt[j];
-      n += e;
-      if (e) {
-        atomicAdd(slice + S_ESCAPED + j - 1, e);
-        if (!BATCH) atomicAdd(probs[0].stats + S_ESCAPED + j - 1, e);
+  }
+  publish(BATCH ? nullptr : probs[0].stats, acc, wcnt + 1, slice);
+}
+
+// ------------------------------------------------- the last, longest walks
+// Once every packet has started and the live ones are fewer than the chip's
+// lanes at one wave per SIMD, a run's time is that of its longest walks, and
+// a wave alone on its SIMD advances by about four cycles per instruction it
+// issues, whether one of its lanes or all 64 take part.  k_walkers therefore
+// gives a wave P = 2^lp packets (walker_waves picks P) and lets all its
+// lanes work for them: in turns of 64/P loop passes,
+//   - every lane computes the draws of one coming event of one packet (they
+//     depend on the packet's index and the event's number alone), with the
+//     functions that need nothing else (logarithms, sines, the phase
+//     function's inverse), and leaves them in LDS;
+//   - the P walking lanes run the passes on those draws and leave what an
+//     event's peel-off needs in LDS;
+//   - every lane runs the peel-off of one recorded event.
+// The same expressions in the same order per packet as k_transport, so the
+// same packets.  Cycles per event of 64 packets against k_transport built for
+// one wave per SIMD: float 3570 against 6170 (slab, no observer) and 3710
+// against 7940 (one observer), double 6650 / 13420 and 6990 / 17870.
+
+// Columns of an event's draws in LDS ([column][64]).
+enum {
+  D_CHANNEL = 0, D_MU, D_LOG_TAU, D_SIN_PHI, D_COS_PHI, D_LOG_PERP, D_SIN_PERP, D_COS_PERP,
+  D_REJ,                    // the first two rejection rounds: 2 x 3 (double) or 2 x 2 (float)
+  D_MU_CORE = D_REJ + 6, D_MU_WING, D_DECAY, N_DRAWS
+};
+
+template <class R, int NL>
+__device__ __forceinline__ void fill_draws(const ProblemK &pb, uint64_t pid, uint32_t event, R *col) {
+  EventRng<R> rng(pb.seed, pid, event);
+  col[D_CHANNEL * 64] = rng.u_small(J_CHANNEL);
+  const R mu = rng.u(J_MU);
+  col[D_MU * 64] = mu;
+  col[D_MU_CORE * 64] = mu_dipole(mu, true);
+  col[D_MU_WING * 64] = mu_dipole(mu, false);
+  R sn, cs;
+  M<R>::sincos2pi(rng.u(J_PHI), &sn, &cs);
+  col[D_SIN_PHI * 64] = sn;
+  col[D_COS_PHI * 64] = cs;
+  col[D_LOG_TAU * 64] = M<R>::log(rng.u(J_TAU));
+  // (float: the base-2 logarithm, scaled where it is used, as M<float>::log does)
+  if constexpr (sizeof(R) == 4) col[D_LOG_PERP * 64] = __builtin_amdgcn_logf(rng.u(J_PERP1));
+  else col[D_LOG_PERP * 64] = M<R>::log(rng.u(J_PERP1));
+  M<R>::sincos2pi(rng.u(J_PERP2), &sn, &cs);
+  col[D_SIN_PERP * 64] = sn;
+  col[D_COS_PERP * 64] = cs;
+  constexpr int n = sizeof(R) == 8 ? 6 : 4;
+#pragma unroll
+  for (int j = 0; j < n; ++j) col[(D_REJ + j) * 64] = rng.u(J_REJ + j);
+  if constexpr (NL > 1) {
+    bool fluor = false;
+#pragma unroll
+    for (int q = 0; q < NL; ++q) fluor = fluor || (q < pb.n_lines && pb.lines[q].n_fluor > 0);
+    if (fluor) col[D_DECAY * 64] = rng.u(J_DECAY);
+  }
+}
+
+// The draws of one event from their columns, as interact takes them.
+template <class R, int NL> struct LdsDraws {
+  const ProblemK &pb;
+  R v[N_DRAWS];
+  __device__ __forceinline__ LdsDraws(const ProblemK &p, const R *col) : pb(p) {
+#pragma unroll
+    for (int j = 0; j < N_DRAWS; ++j)
+      if ((j < D_REJ || j >= D_MU_CORE || j < D_REJ + (sizeof(R) == 8 ? 6 : 4)) && (NL > 1 || j != D_DECAY))
+        v[j] = col[j * 64];
+  }
+  __device__ __forceinline__ R channel() const { return v[D_CHANNEL]; }
+  __device__ __forceinline__ R albedo() const { return v[D_REJ]; }   // J_ALBEDO is the first round's first draw
+  __device__ __forceinline__ R mu() const { return v[D_MU]; }
+  __device__ __forceinline__ R log_tau() const { return v[D_LOG_TAU]; }
+  __device__ __forceinline__ void line() const {}
+  __device__ __forceinline__ R log_perp() const {
+    return sizeof(R) == 4 ? v[D_LOG_PERP] * R(0.69314718055994531) : v[D_LOG_PERP];
+  }
+  __device__ __forceinline__ void perp(R *sp, R *cp) const { *sp = v[D_SIN_PERP]; *cp = v[D_COS_PERP]; }
+  __device__ __forceinline__ void phi(R *sp, R *cp) const { *sp = v[D_SIN_PHI]; *cp = v[D_COS_PHI]; }
+  __device__ __forceinline__ void phi_dust(R *sp, R *cp) const { phi(sp, cp); }
+  __device__ __forceinline__ R decay() const { return v[D_DECAY]; }
+  __device__ __forceinline__ R dipole(bool core) const { return core ? v[D_MU_CORE] : v[D_MU_WING]; }
+  __device__ __forceinline__ bool round(const UparEnv<R> &e, R a, int it, R *out) const {
+    if constexpr (sizeof(R) == 4) return upar_try_pair(e, a, v[D_REJ + 2 * it], v[D_REJ + 2 * it + 1], out);
+    else return upar_try_triple(e, a, v[D_REJ + 3 * it], v[D_REJ + 3 * it + 1], v[D_REJ + 3 * it + 2], out);
+  }
+  // From round s.rej on (not 0 for an event that a regrouped launch left
+  // pending); the rounds beyond the second draw their own numbers.
+  __device__ __forceinline__ bool upar(Lane<R> &s, R x, R a, R la, R *out) const {
+    uint32_t it = s.rej;
+    s.rej = 0;
+    if (fabs(x) >= R(8)) {
+      *out = upar_gauss<R>(x, v[D_REJ], v[D_REJ + 1]);
+      return true;
+    }
+    const UparEnv<R> e = upar_env(x, a, la);
+    if (it == 0 && round(e, a, 0, out)) return true;
+    if (it <= 1 && round(e, a, 1, out)) return true;
+    EventRng<R> rng(pb.seed, (uint64_t)s.pid, s.event);
+    for (it = it < 2 ? 2 : it; it < MAX_REJECT; ++it)
+      if (upar_try(e, a, rng, it, out)) return true;
+    return false;
+  }
+  static __device__ __forceinline__ int undrawn(Lane<R> &) { return ST_STUCK; }
+};
+
+// What an event's peel-off needs, in LDS ([column][64]): the event's point,
+// its source (direction in, frequency, atom velocity; dust keeps k_in . u in
+// the first velocity) and its cell.
+template <class R> struct PeelCols {
+  double p[3 * 64];
+  R v[7 * 64];       // k_in, x, U
+  int i[6 * 64];     // kind | line << 4 | core << 8 (-1: none), leaf, level, origin
+};
+
+template <class R>
+__device__ __forceinline__ void record_peel(PeelCols<R> &c, int j, const Lane<R> &s, const PeelSrc<R> &ps) {
+  const bool dust = ps.kind == 2;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    c.p[d * 64 + j] = s.p[d];
+    c.v[d * 64 + j] = ps.kin[d];
+  }
+  c.v[3 * 64 + j] = ps.x;
+  c.v[4 * 64 + j] = dust ? ps.w : ps.U[0];
+  if (!dust) {
+    c.v[5 * 64 + j] = ps.U[1];
+    c.v[6 * 64 + j] = ps.U[2];
+  }
+  c.i[j] = dust ? ps.kind : ps.kind | (ps.line << 4) | (ps.core << 8);
+  c.i[64 + j] = s.c.leaf;
+  c.i[2 * 64 + j] = s.c.level;
+  c.i[3 * 64 + j] = s.c.ox;
+  c.i[4 * 64 + j] = s.c.oy;
+  c.i[5 * 64 + j] = s.c.oz;
+}
+
+template <class R, int NL>
+__device__ __forceinline__ void peel_recorded(const ProblemK &pb, const PeelCols<R> &c, int j, LaneCount &cnt,
+                                              const PeelSink<R> &snk) {
+  const int code = c.i[j];
+  PeelSrc<R> ps;
+  ps.kind = code & 15;
+  ps.line = (code >> 4) & 15;
+  ps.core = code >> 8;
+  const double p[3] = {c.p[j], c.p[64 + j], c.p[2 * 64 + j]};
+  const Cell cell{c.i[64 + j], c.i[2 * 64 + j], c.i[3 * 64 + j], c.i[4 * 64 + j], c.i[5 * 64 + j]};
+  const LeafRec<R> lf = load_leaf<R>(pb.leaves, cell.leaf);
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    ps.kin[d] = c.v[d * 64 + j];
+    ps.U[d] = c.v[(4 + d) * 64 + j];
+  }
+  ps.x = c.v[3 * 64 + j];
+  ps.w = ps.U[0];
+  ps.ux = lf.ux; ps.uy = lf.uy; ps.uz = lf.uz;
+  ps.irho = lf.irho;
+  ps.rho = M<R>::div(R(1), lf.irho);
+  const LineK &ln = pb.lines[ps.kind == 2 ? 0 : ps.line];
+  ps.bc = cst<R>(pb.b_ref, pb.b_ref_f) * cst<R>(ln.mu, ln.f.mu) * ps.rho;
+  const StartCell<R> sc{&cell, &lf, nullptr};
+  peel_all<R, true, NL>(pb, p, ps, nullptr, 0, cnt, snk, &sc);
+}
+
+// One wave per block; wave w walks slots [w P, w P + P), all of one problem,
+// and queues peel-off rays in region region0 + w.
+template <class R, bool BATCH, int NL>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1)))
+    k_walkers(const ProblemK *__restrict__ probs, int region0, SlotState *__restrict__ slots, int lp, int budget,
+              unsigned long long *__restrict__ slice) {
+  extern __shared__ int lds[];
+  __shared__ R draws[N_DRAWS * 64];
+  __shared__ PeelCols<R> rec;
+  __shared__ int walker_cnt[3 * 64];   // peel-off rays, leaves crossed and dropped deposits of each walker's turn
+  __shared__ int wcnt[4];              // queued rays, then the packets that escaped, were absorbed, got stuck
+  const int lane = threadIdx.x;
+  const int P = 1 << lp, K = 64 >> lp;
+  int *stk = lds + lane;
+  Lane<R> s, z;
+  SliceCount acc{0, 0, 0, 0, 0};
+  int prob = 0, fin = ST_NONE;
+  bool active = false;
+  SlotState &q = slots[(int64_t)blockIdx.x * P + (lane & (P - 1))];
+  if (lane < P && q.active) {
+    load_slot<R>(q, s, &prob);
+    active = true;
+  }
+  if (lane < 4) wcnt[lane] = 0;
+  for (int j = lane; j < 3 * 64; j += 64) walker_cnt[j] = 0;
+  PeelQueue *const pq = probs[0].pq;
+  const bool queue = pq != nullptr;
+  const int region = region0 + (int)blockIdx.x;
+  const unsigned long long live = __ballot(active);
+  if (live == 0ull) {
+    if (queue && lane == 0) pq->counts[region] = 0u;
+    return;
+  }
+  if (BATCH) prob = __builtin_amdgcn_readfirstlane(__shfl(prob, __ffsll((long long)live) - 1));
+  const ProblemK &pb = probs[BATCH ? prob : 0];
+  if (active) {
+    const int X[3] = {s.c.ox, s.c.oy, s.c.oz};
+    locate(pb, X, stk, 64, s.c);
+    s.lf = load_leaf<R>(pb.leaves, s.c.leaf);
+    z = s;
+    if (s.rej) --s.event;   // a pending event is taken up again as the next one
+  }
+  PeelSink<R> snk;
+  snk.count = wcnt;
+  snk.region = queue ? (PeelJob<R> *)pq->jobs + (size_t)region * pq->cap : nullptr;
+  snk.cap = queue ? (uint32_t)pq->cap : 0u;
+  snk.lost = queue ? &pq->lost : nullptr;
+  const int room = queue ? (int)pq->cap - 64 * MAX_OBS : 0x7fffffff;
+  __syncthreads();
+  for (int it = 0; it < budget; it += K) {
+    const unsigned long long walking = __ballot(active);
+    if (walking == 0ull || wcnt[0] > room) break;
+    // ---- the draws of the coming events, one per lane
+    {
+      const int w = lane & (P - 1);
+      const uint32_t plo = (uint32_t)__shfl((int)(uint32_t)s.pid, w), phi = (uint32_t)__shfl((int)(uint32_t)(s.pid >> 32), w);
+      const uint32_t ev = (uint32_t)__shfl((int)s.event, w);
+      if ((walking >> w) & 1ull)
+        fill_draws<R, NL>(pb, (uint64_t)phi << 32 | plo, ev + 1u + (uint32_t)(lane >> lp), draws + lane);
+      rec.i[lane] = -1;
+    }
+    __syncthreads();
+    // ---- the walkers' passes
+    const int turn = budget - it < K ? budget - it : K;
+    int used = lane;   // this lane's next column of draws
+    for (int b = 0; active && b < turn; ++b) {
+      Opac<R, NL> o;
+      opacity(pb, s.lf, (double)s.x, s.k, o);
+      double face[3], lo[3], hi[3];
+      int em = 0;
+      double te = 0.0, td = 0.0, lmax = 0.0, tseg = 0.0;
+      const bool pend = s.rej != 0;
+      bool here = pend || (s.lf.bnd == R(0) && s.tau < (double)o.ktot * inner_dist(s.c, pb.L, s.p));
+      if (here) {
+        cell_bounds(s.c, pb.L, lo, hi);
+      } else {
+        te = exit_dist(s.c, pb.L, s.p, s.kd, face, lo, hi, &em);
+        td = domain_dist_leaf(s.lf, pb.domain, pb.dom, s.p, s.kd);
+        lmax = te < td ? te : td;
+        tseg = (double)o.ktot * lmax;
+        here = s.tau < tseg;
+      }
+      int st = ST_NONE;
+      if (here) {
+        const double dist = pend ? 0.0
+                                 : (sizeof(R) == 4 ? s.tau * (double)__builtin_amdgcn_rcpf((float)o.ktot)
+                                                   : s.tau / (double)o.ktot);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) s.p[d] = fmin(fmax(fma(dist, s.kd[d], s.p[d]), lo[d]), hi[d]);
+        s.path += dist;
+        ++s.event;
+        if (!pend && pb.max_events > 0 && (int64_t)s.event >= pb.max_events) {
+          st = ST_STUCK;
+        } else {
+          LdsDraws<R, NL> dr(pb, draws + used);
+          st = interact<R, NL>(pb, s, o, dr, [&](const PeelSrc<R> &ps) { record_peel(rec, used, s, ps); });
+          used += P;
+        }
+      } else {
+        s.tau -= tseg;
+        s.path += lmax;
+        ++s.cnt.cross;
+        if (s.cnt.cross >= MAX_CROSS) {
+          st = ST_STUCK;
+        } else if (td <= te) {
+#pragma unroll
+          for (int d = 0; d < 3; ++d) s.p[d] = fma(td, s.kd[d], s.p[d]);
+          st = ST_ESCAPED;
+        } else {
+          double pn[3];
+          exit_point(te, em, s.p, s.kd, face, lo, hi, pn);
+          s.p[0] = pn[0]; s.p[1] = pn[1]; s.p[2] = pn[2];
+          wrap_slab(pb.domain, s.p, s.kd);
+          int X[3];
+          if (!int_coords(pb.L, s.p, s.kd, X)) {
+            st = ST_ESCAPED;
+          } else {
+            relocate(pb, X, stk, 64, s.c);
+            s.lf = load_leaf<R>(pb.leaves, s.c.leaf);
+          }
+        }
+      }
+      if (st != ST_NONE) {
+        fin = st;
+        active = false;
       }
     }
-    if (n) {
-      atomicAdd(slice + S_EMITTED, n);
-      if (!BATCH) atomicAdd(probs[0].stats + S_EMITTED, n);
+    __syncthreads();
+    // ---- the peel-off of the turn's events, one per lane
+    if (pb.n_obs) {
+      if (rec.i[lane] >= 0) {
+        LaneCount c{0, 0, 0, 0, 0};
+        peel_recorded<R, NL>(pb, rec, lane, c, snk);
+        const int w = lane & (P - 1);
+        atomicAdd(walker_cnt + w, (int)c.peel_rays);
+        if (c.peel_cross) atomicAdd(walker_cnt + 64 + w, (int)c.peel_cross);
+        if (c.peel_drop) atomicAdd(walker_cnt + 128 + w, (int)c.peel_drop);
+      }
+      __syncthreads();
+      if (lane < P) {
+        s.cnt.peel_rays += (uint32_t)walker_cnt[lane];
+        s.cnt.peel_cross += (uint32_t)walker_cnt[64 + lane];
+        s.cnt.peel_drop += (uint32_t)walker_cnt[128 + lane];
+        walker_cnt[lane] = walker_cnt[64 + lane] = walker_cnt[128 + lane] = 0;
+      }
     }
-  }
-  unsigned long long v[5] = {acc.scat, acc.dust, acc.cross, acc.peel_rays, acc.peel_cross};
-  const int idx[5] = {S_SCAT, S_DUST_SCAT, S_CROSS, S_PEEL_RAYS, S_PEEL_CROSS};
-#pragma unroll
-  for (int j = 0; j < 5; ++j) {
-    unsigned long long x = v[j];
-    for (int off = 32; off > 0; off >>= 1) x += __shfl_down(x, off);
-    if (lane == 0 && x) {
-      atomicAdd(slice + idx[j], x);
-      if (!BATCH) atomicAdd(probs[0].stats + idx[j], x);
+    if (fin != ST_NONE) {
+      add_delta(acc, s, z);
+      finish<R, BATCH>(pb, s, fin, wcnt + 1, slice);
+      fin = ST_NONE;
+      if (lane < P) q.active = 0;
     }
+    __syncthreads();
   }
+  if (active) {
+    if (s.rej) ++s.event;   // not reached: still pending
+    save_slot<R>(q, s, prob);
+    add_delta(acc, s, z);
+  }
+  if (queue && lane == 0) pq->counts[region] = (uint32_t)wcnt[0];
+  publish(BATCH ? nullptr : pb.stats, acc, wcnt + 1, slice);
 }
 
 // Number of slots (lanes) holding a packet after a launch.
@@ -1113,6 +1495,53 @@ __global__ void k_compact_slots(const SlotState *__restrict__ src, int64_t n, Sl
   if (lane == leader) base = atomicAdd(n_live, (unsigned long long)__popcll(m));
   base = __shfl(base, leader);
   if (act) dst[base + (unsigned long long)__popcll(m & ((1ull << lane) - 1ull))] = src[i];
+}
+
+// The same for a batch, each problem's packets in slots of their own, a
+// multiple of P of them, so that every wave of k_walkers holds packets of one
+// problem: work[p] counts problem p's live packets (k_group_count), becomes
+// its first slot (k_group_offsets), then its next free one (k_group_slots).
+__global__ void k_group_count(const SlotState *__restrict__ src, int64_t n, uint32_t *work) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n && src[i].active) atomicAdd(work + src[i].prob, 1u);
+}
+
+__global__ void __launch_bounds__(1024) k_group_offsets(uint32_t *work, int n_probs, int lp,
+                                                        unsigned long long *n_live) {
+  __shared__ uint32_t part[16];
+  const int lane = __lane_id(), wave = threadIdx.x >> 6;
+  uint32_t base = 0, live = 0;
+  for (int b = 0; b < n_probs; b += 1024) {
+    const int p = b + (int)threadIdx.x;
+    const uint32_t c = p < n_probs ? work[p] : 0u;
+    const uint32_t v = ((c + (1u << lp) - 1u) >> lp) << lp;
+    live += c;
+    uint32_t x = v;
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t y = __shfl_up(x, off);
+      if (lane >= off) x += y;
+    }
+    if (lane == 63) part[wave] = x;
+    __syncthreads();
+    uint32_t before = base, all = base;
+    for (int w = 0; w < 16; ++w) {
+      if (w < wave) before += part[w];
+      all += part[w];
+    }
+    if (p < n_probs) work[p] = before + x - v;
+    base = all;
+    __syncthreads();
+  }
+  for (int off = 32; off > 0; off >>= 1) live += __shfl_xor(live, off);
+  if (lane == 0 && live) atomicAdd(n_live, (unsigned long long)live);
+}
+
+__global__ void k_group_slots(const SlotState *__restrict__ src, int64_t n, SlotState *__restrict__ dst, int64_t n_dst,
+                              uint32_t *work) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n || !src[i].active) return;
+  const int64_t j = atomicAdd(work + src[i].prob, 1u);
+  if (j < n_dst) dst[j] = src[i];
 }
 
 // Before the ray-cast pass: offs[r] = jobs queued in regions 0 .. r - 1 of the
@@ -1217,9 +1646,13 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DrainW
   const uint32_t share = total / (gridDim.x * (blockDim.x / 64) * 8u);
   const uint32_t run = share < 64u ? 64u : (share > 1024u ? 1024u : share);
   const double cut = TauCut<R>::v;
-  // wave-uniform: next job and end of the wave's run, the region of the next
-  // job, its first job and its end (running indices)
-  uint32_t cur = 0, end = 0, reg = 0, r_beg = 0, r_end = 0;
+  // wave-uniform: next job and end of the wave's run (its first one by its
+  // index, the next ones from pq->take), the region of the next job, its first
+  // job and its end (running indices)
+  const uint32_t wave = (uint32_t)blockIdx.x * (blockDim.x / 64) + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint32_t waves = gridDim.x * (blockDim.x / 64);
+  if ((unsigned long long)wave * run >= total) return;
+  uint32_t cur = wave * run, end = total - cur < run ? total : cur + run, reg = 0, r_beg = 0, r_end = 0;
   bool drained = false;
   bool active = false;
   int prob = 0, acc_prob = 0;
@@ -1237,7 +1670,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DrainW
       if (cur >= end) {
         unsigned long long t = 0;
         if (lane == 0) t = atomicAdd(&pq->take, (unsigned long long)run);
-        t = __shfl(t, 0);
+        t = __shfl(t, 0) + (unsigned long long)waves * run;
         if (t >= total) {
           drained = true;
           break;
@@ -1915,25 +2348,23 @@ using TransportFn = void (*)(const ProblemK *, const int64_t *, int, unsigned lo
                             int, unsigned long long *);
 
 // The one-round-per-pass form (regroup) is built for the deferred
-// peel-off kernels only (the default); the one-wave tail form for the
-// single-problem deferred kernels.
+// peel-off kernels only (the default).
 template <class R, int NL>
-static TransportFn transport_fn(bool batch, bool defer, bool regroup, bool tail) {
+static TransportFn transport_fn(bool batch, bool defer, bool regroup) {
   if (batch) {
     if (!defer) return k_transport<R, true, false, NL>;
     return regroup ? k_transport<R, true, true, NL, true> : k_transport<R, true, true, NL>;
   }
   if (!defer) return k_transport<R, false, false, NL>;
-  if (tail) return regroup ? k_transport<R, false, true, NL, true, true> : k_transport<R, false, true, NL, false, true>;
   return regroup ? k_transport<R, false, true, NL, true> : k_transport<R, false, true, NL>;
 }
 
-static TransportFn transport_fn(bool fp32, bool batch, bool defer, bool one_line, bool regroup, bool tail = false) {
+static TransportFn transport_fn(bool fp32, bool batch, bool defer, bool one_line, bool regroup) {
   if (fp32)
-    return one_line ? transport_fn<float, 1>(batch, defer, regroup, tail)
-                    : transport_fn<float, MAX_LINES>(batch, defer, regroup, tail);
-  return one_line ? transport_fn<double, 1>(batch, defer, regroup, tail)
-                  : transport_fn<double, MAX_LINES>(batch, defer, regroup, tail);
+    return one_line ? transport_fn<float, 1>(batch, defer, regroup)
+                    : transport_fn<float, MAX_LINES>(batch, defer, regroup);
+  return one_line ? transport_fn<double, 1>(batch, defer, regroup)
+                  : transport_fn<double, MAX_LINES>(batch, defer, regroup);
 }
 
 static size_t transport_lds(int stack_levels, int block) {
@@ -1943,10 +2374,38 @@ static size_t transport_lds(int stack_levels, int block) {
 hipError_t launch_transport(bool fp32, bool batch, bool defer, bool one_line, bool regroup, const ProblemK *d_probs,
                             const int64_t *d_starts, int n_probs, unsigned long long *d_next, int refill_min,
                             int stack_levels, int grid, int block, void *slots, int budget,
-                            unsigned long long *slice, hipStream_t st, bool tail) {
-  hipLaunchKernelGGL(transport_fn(fp32, batch, defer, one_line, regroup, tail), dim3(grid), dim3(block),
+                            unsigned long long *slice, hipStream_t st) {
+  hipLaunchKernelGGL(transport_fn(fp32, batch, defer, one_line, regroup), dim3(grid), dim3(block),
                      transport_lds(stack_levels, block), st,
                      d_probs, d_starts, n_probs, d_next, refill_min, stack_levels, (SlotState *)slots, budget, slice);
+  return hipGetLastError();
+}
+
+template <class R>
+static void launch_walkers_as(bool batch, bool one_line, const ProblemK *d_probs, int region0, int levels,
+                              SlotState *slots, int lp, int waves, int budget, unsigned long long *slice,
+                              hipStream_t st) {
+  const auto fn = batch ? (one_line ? k_walkers<R, true, 1> : k_walkers<R, true, MAX_LINES>)
+                        : (one_line ? k_walkers<R, false, 1> : k_walkers<R, false, MAX_LINES>);
+  hipLaunchKernelGGL(fn, dim3(waves), dim3(64), (size_t)levels * 64 * sizeof(int), st, d_probs, region0, slots, lp,
+                     budget, slice);
+}
+
+hipError_t launch_walkers(bool fp32, bool batch, bool one_line, const ProblemK *d_probs, int region0, int stack_levels,
+                          void *slots, int lp, int waves, int budget, unsigned long long *slice, hipStream_t st) {
+  SlotState *s = (SlotState *)slots;
+  if (fp32) launch_walkers_as<float>(batch, one_line, d_probs, region0, stack_levels, s, lp, waves, budget, slice, st);
+  else launch_walkers_as<double>(batch, one_line, d_probs, region0, stack_levels, s, lp, waves, budget, slice, st);
+  return hipGetLastError();
+}
+
+hipError_t launch_group_slots(const void *src, int64_t n, void *dst, int64_t n_dst, int n_probs, int lp, uint32_t *work,
+                              unsigned long long *n_live, hipStream_t st) {
+  if (n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_group_count, dim3(blocks_for(n, 256)), dim3(256), 0, st, (const SlotState *)src, n, work);
+  hipLaunchKernelGGL(k_group_offsets, dim3(1), dim3(1024), 0, st, work, n_probs, lp, n_live);
+  hipLaunchKernelGGL(k_group_slots, dim3(blocks_for(n, 256)), dim3(256), 0, st, (const SlotState *)src, n,
+                     (SlotState *)dst, n_dst, work);
   return hipGetLastError();
 }
 

@@ -12,12 +12,20 @@ namespace rmc {
 // problem of the launch has a single line (a kernel specialised for it).
 // regroup (with defer): one rejection round of a line scattering per pass
 // of the loop, a rejected round leaving the event pending for the next.
-// tail (single problem, defer): the kernel compiled for one wave per SIMD,
-// for grids of at most one wave per SIMD.
 hipError_t launch_transport(bool fp32, bool batch, bool defer, bool one_line, bool regroup, const ProblemK *d_probs,
                             const int64_t *d_starts, int n_probs, unsigned long long *d_next, int refill_min,
                             int stack_levels, int grid, int block, void *slots, int budget,
-                            unsigned long long *slice, hipStream_t st, bool tail = false);
+                            unsigned long long *slice, hipStream_t st);
+// The transport of the last packets (defer): `waves` waves of 2^lp slots each,
+// every wave's slots of one problem; no packet is taken from the queue.  Their
+// peel-off rays go to regions region0 .. region0 + waves - 1.
+hipError_t launch_walkers(bool fp32, bool batch, bool one_line, const ProblemK *d_probs, int region0, int stack_levels,
+                          void *slots, int lp, int waves, int budget, unsigned long long *slice, hipStream_t st);
+// active slots of src[0, n) copied to dst[0, n_dst) (cleared), each of the
+// n_probs problems' in slots of its own, a multiple of 2^lp of them; work:
+// n_probs zeros; *n_live += their count
+hipError_t launch_group_slots(const void *src, int64_t n, void *dst, int64_t n_dst, int n_probs, int lp, uint32_t *work,
+                              unsigned long long *n_live, hipStream_t st);
 size_t slot_bytes();
 // Index of the jobs in the peel-off queue pq (a device PeelQueue) whose first
 // n_regions regions the last transport launch filled, then the ray-cast pass
