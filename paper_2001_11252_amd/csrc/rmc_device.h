@@ -172,6 +172,39 @@ struct ProblemK {
   int index;                // position in the launch's problem array
 };
 
+// Line i of a problem, for a line index of each lane's own.
+__device__ __forceinline__ const LineK &line_of(const ProblemK &pb, int i) { return pb.lines[i]; }
+
+// What a packet's walk reads of its problem, copied into registers once per
+// launch: a wave alone on its SIMD waits for every scalar load, and the
+// compiler cannot keep them across the walk's stores and barriers.  With
+// several lines, shared holds them for a line index of each lane's own.
+template <int NL> struct WalkK {
+  const int32_t *nodes, *top;
+  const void *leaves;
+  int L, top_level, n_lines, n_obs, domain, forward_only, voigt_exact;
+  LineK lines[NL];
+  const LineK *shared;
+  double b_ref, dom[4], albedo, g_hg, skip_tau, skip_frac;
+  float b_ref_f, albedo_f, g_hg_f;
+  int64_t max_events;
+  uint64_t seed;
+  __device__ __forceinline__ WalkK(const ProblemK &p, const LineK *sh)
+      : nodes(p.nodes), top(p.top), leaves(p.leaves), L(p.L), top_level(p.top_level), n_lines(p.n_lines),
+        n_obs(p.n_obs), domain(p.domain), forward_only(p.forward_only), voigt_exact(p.voigt_exact), shared(sh),
+        b_ref(p.b_ref), albedo(p.albedo), g_hg(p.g_hg), skip_tau(p.skip_tau), skip_frac(p.skip_frac),
+        b_ref_f(p.b_ref_f), albedo_f(p.albedo_f), g_hg_f(p.g_hg_f), max_events(p.max_events), seed(p.seed) {
+#pragma unroll
+    for (int i = 0; i < NL; ++i) lines[i] = p.lines[i];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) dom[d] = p.dom[d];
+  }
+};
+template <int NL> __device__ __forceinline__ const LineK &line_of(const WalkK<NL> &pb, int i) {
+  if constexpr (NL == 1) return pb.lines[0];
+  else return pb.shared[i];
+}
+
 // ------------------------------------------------------------------ Philox
 // Philox4x32-10 (Salmon, Moraes, Dror & Shaw, SC'11).  Each round's two
 // 32x32-bit products are taken whole as 64-bit products: one
@@ -902,10 +935,12 @@ __device__ __forceinline__ void relocate(const int32_t *__restrict__ nodes, cons
   descend_from(nodes, top, T, L, L - 1 - b, X, stack, stride, c);   // from the common ancestor's level
 }
 
-__device__ __forceinline__ void locate(const ProblemK &pb, const int X[3], int *stack, int stride, Cell &c) {
+template <class PB>
+__device__ __forceinline__ void locate(const PB &pb, const int X[3], int *stack, int stride, Cell &c) {
   locate(pb.nodes, pb.top, pb.top_level, pb.L, X, stack, stride, c);
 }
-__device__ __forceinline__ void relocate(const ProblemK &pb, const int X[3], int *stack, int stride, Cell &c) {
+template <class PB>
+__device__ __forceinline__ void relocate(const PB &pb, const int X[3], int *stack, int stride, Cell &c) {
   relocate(pb.nodes, pb.top, pb.top_level, pb.L, X, stack, stride, c);
 }
 
@@ -954,8 +989,8 @@ template <class R, int NL = MAX_LINES> struct Opac {
 // The numerator delta + s x_ext - w is formed in double in both precisions:
 // for gas moving many thermal widths it is a small difference of large
 // terms, and float would lose the core of the profile.
-template <class R, int NL>
-__device__ __forceinline__ void opacity(const ProblemK &pb, const LeafRec<R> &lf, double x_ext, const R k[3],
+template <class R, int NL, class PB>
+__device__ __forceinline__ void opacity(const PB &pb, const LeafRec<R> &lf, double x_ext, const R k[3],
                                         Opac<R, NL> &o) {
   const double wd = (double)k[0] * (double)lf.ux + (double)k[1] * (double)lf.uy + (double)k[2] * (double)lf.uz;
   o.w = (R)wd;
@@ -992,8 +1027,8 @@ __device__ __forceinline__ void opacity(const ProblemK &pb, const LeafRec<R> &lf
 // skip_tau thick) and skip_frac (a tau_c)^(1/3) (a fraction of the wing
 // frequency at which a medium of the cell's depth lets packets out).
 // Returns x_crit^2 while |x| < x_crit, else 0 (the unbiased draw).
-template <class R>
-__device__ __forceinline__ R core_skip_x2(const ProblemK &pb, const LineK &ln, const LeafRec<R> &lf, int level,
+template <class R, class PB>
+__device__ __forceinline__ R core_skip_x2(const PB &pb, const LineK &ln, const LeafRec<R> &lf, int level,
                                           R a, R x) {
   const R tc = lf.nl * cst<R>(ln.kfac, ln.f.kfac) * (R)ldexp(1.0, -level);
   const R ts = R(pb.skip_tau);

@@ -623,8 +623,8 @@ template <class R, bool REGROUP> struct RngDraws {
 // draw per call: a rejected round leaves the event pending (s.rej rounds
 // run) and the packet where it is, and the next pass of the transport loop
 // calls again for the next round (the same draws as the looping sampler).
-template <class R, int NL, class D, class P>
-__device__ __forceinline__ int interact(const ProblemK &pb, Lane<R> &s, const Opac<R, NL> &o, D &dr, P &&peel) {
+template <class R, int NL, class PB, class D, class P>
+__device__ __forceinline__ int interact(const PB &pb, Lane<R> &s, const Opac<R, NL> &o, D &dr, P &&peel) {
   R r = dr.channel() * o.ktot;
   const R kin[3] = {s.k[0], s.k[1], s.k[2]};
   // the pair perpendicular to k_in is formed where it is used (after the
@@ -677,7 +677,7 @@ __device__ __forceinline__ int interact(const ProblemK &pb, Lane<R> &s, const Op
         }
       }
     }
-    const LineK &ln = pb.lines[i];
+    const LineK &ln = line_of(pb, i);
     const R a = cst<R>(ln.alpha, ln.f.alpha) * s.lf.irho;
     // log10 a for the envelope: the double path adds the line's log10 alpha
     // and the leaf's log10(1/rho) (its record holds it)
@@ -1198,9 +1198,9 @@ __device__ __forceinline__ void fill_draws(const ProblemK &pb, uint64_t pid, uin
 
 // The draws of one event from their columns, as interact takes them.
 template <class R, int NL> struct LdsDraws {
-  const ProblemK &pb;
+  uint64_t seed;
   R v[N_DRAWS];
-  __device__ __forceinline__ LdsDraws(const ProblemK &p, const R *col) : pb(p) {
+  __device__ __forceinline__ LdsDraws(uint64_t sd, const R *col) : seed(sd) {
 #pragma unroll
     for (int j = 0; j < N_DRAWS; ++j)
       if ((j < D_REJ || j >= D_MU_CORE || j < D_REJ + (sizeof(R) == 8 ? 6 : 4)) && (NL > 1 || j != D_DECAY))
@@ -1235,7 +1235,7 @@ template <class R, int NL> struct LdsDraws {
     const UparEnv<R> e = upar_env(x, a, la);
     if (it == 0 && round(e, a, 0, out)) return true;
     if (it <= 1 && round(e, a, 1, out)) return true;
-    EventRng<R> rng(pb.seed, (uint64_t)s.pid, s.event);
+    EventRng<R> rng(seed, (uint64_t)s.pid, s.event);
     for (it = it < 2 ? 2 : it; it < MAX_REJECT; ++it)
       if (upar_try(e, a, rng, it, out)) return true;
     return false;
@@ -1336,10 +1336,15 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1)))
   }
   if (BATCH) prob = __builtin_amdgcn_readfirstlane(__shfl(prob, __ffsll((long long)live) - 1));
   const ProblemK &pb = probs[BATCH ? prob : 0];
+  __shared__ LineK lines[NL];
+  if (NL > 1) {
+    for (int j = lane; j < (int)(NL * sizeof(LineK) / 4); j += 64) ((uint32_t *)lines)[j] = ((const uint32_t *)pb.lines)[j];
+  }
+  const WalkK<NL> wk(pb, lines);
   if (active) {
     const int X[3] = {s.c.ox, s.c.oy, s.c.oz};
-    locate(pb, X, stk, 64, s.c);
-    s.lf = load_leaf<R>(pb.leaves, s.c.leaf);
+    locate(wk, X, stk, 64, s.c);
+    s.lf = load_leaf<R>(wk.leaves, s.c.leaf);
     z = s;
     if (s.rej) --s.event;   // a pending event is taken up again as the next one
   }
@@ -1368,17 +1373,17 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1)))
     int used = lane;   // this lane's next column of draws
     for (int b = 0; active && b < turn; ++b) {
       Opac<R, NL> o;
-      opacity(pb, s.lf, (double)s.x, s.k, o);
+      opacity(wk, s.lf, (double)s.x, s.k, o);
       double face[3], lo[3], hi[3];
       int em = 0;
       double te = 0.0, td = 0.0, lmax = 0.0, tseg = 0.0;
       const bool pend = s.rej != 0;
-      bool here = pend || (s.lf.bnd == R(0) && s.tau < (double)o.ktot * inner_dist(s.c, pb.L, s.p));
+      bool here = pend || (s.lf.bnd == R(0) && s.tau < (double)o.ktot * inner_dist(s.c, wk.L, s.p));
       if (here) {
-        cell_bounds(s.c, pb.L, lo, hi);
+        cell_bounds(s.c, wk.L, lo, hi);
       } else {
-        te = exit_dist(s.c, pb.L, s.p, s.kd, face, lo, hi, &em);
-        td = domain_dist_leaf(s.lf, pb.domain, pb.dom, s.p, s.kd);
+        te = exit_dist(s.c, wk.L, s.p, s.kd, face, lo, hi, &em);
+        td = domain_dist_leaf(s.lf, wk.domain, wk.dom, s.p, s.kd);
         lmax = te < td ? te : td;
         tseg = (double)o.ktot * lmax;
         here = s.tau < tseg;
@@ -1392,11 +1397,11 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1)))
         for (int d = 0; d < 3; ++d) s.p[d] = fmin(fmax(fma(dist, s.kd[d], s.p[d]), lo[d]), hi[d]);
         s.path += dist;
         ++s.event;
-        if (!pend && pb.max_events > 0 && (int64_t)s.event >= pb.max_events) {
+        if (!pend && wk.max_events > 0 && (int64_t)s.event >= wk.max_events) {
           st = ST_STUCK;
         } else {
-          LdsDraws<R, NL> dr(pb, draws + used);
-          st = interact<R, NL>(pb, s, o, dr, [&](const PeelSrc<R> &ps) { record_peel(rec, used, s, ps); });
+          LdsDraws<R, NL> dr(wk.seed, draws + used);
+          st = interact<R, NL>(wk, s, o, dr, [&](const PeelSrc<R> &ps) { record_peel(rec, used, s, ps); });
           used += P;
         }
       } else {
@@ -1413,13 +1418,13 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1)))
           double pn[3];
           exit_point(te, em, s.p, s.kd, face, lo, hi, pn);
           s.p[0] = pn[0]; s.p[1] = pn[1]; s.p[2] = pn[2];
-          wrap_slab(pb.domain, s.p, s.kd);
+          wrap_slab(wk.domain, s.p, s.kd);
           int X[3];
-          if (!int_coords(pb.L, s.p, s.kd, X)) {
+          if (!int_coords(wk.L, s.p, s.kd, X)) {
             st = ST_ESCAPED;
           } else {
-            relocate(pb, X, stk, 64, s.c);
-            s.lf = load_leaf<R>(pb.leaves, s.c.leaf);
+            relocate(wk, X, stk, 64, s.c);
+            s.lf = load_leaf<R>(wk.leaves, s.c.leaf);
           }
         }
       }
@@ -1430,7 +1435,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1)))
     }
     __syncthreads();
     // ---- the peel-off of the turn's events, one per lane
-    if (pb.n_obs) {
+    if (wk.n_obs) {
       if (rec.i[lane] >= 0) {
         LaneCount c{0, 0, 0, 0, 0};
         peel_recorded<R, NL>(pb, rec, lane, c, snk);
