@@ -2364,43 +2364,47 @@ static TransportFn transport_fn(bool batch, bool defer, bool regroup) {
   return regroup ? k_transport<R, false, true, NL, true> : k_transport<R, false, true, NL>;
 }
 
-static TransportFn transport_fn(bool fp32, bool batch, bool defer, bool one_line, bool regroup) {
+static TransportFn transport_fn(bool fp32, bool batch, bool defer, int nl, bool regroup) {
   if (fp32)
-    return one_line ? transport_fn<float, 1>(batch, defer, regroup)
-                    : transport_fn<float, MAX_LINES>(batch, defer, regroup);
-  return one_line ? transport_fn<double, 1>(batch, defer, regroup)
-                  : transport_fn<double, MAX_LINES>(batch, defer, regroup);
+    return nl == 1   ? transport_fn<float, 1>(batch, defer, regroup)
+           : nl == 2 ? transport_fn<float, 2>(batch, defer, regroup)
+                     : transport_fn<float, MAX_LINES>(batch, defer, regroup);
+  return nl == 1   ? transport_fn<double, 1>(batch, defer, regroup)
+         : nl == 2 ? transport_fn<double, 2>(batch, defer, regroup)
+                   : transport_fn<double, MAX_LINES>(batch, defer, regroup);
 }
 
 static size_t transport_lds(int stack_levels, int block) {
   return ((size_t)2 * stack_levels * block + 4 * (block / 64)) * sizeof(int);
 }
 
-hipError_t launch_transport(bool fp32, bool batch, bool defer, bool one_line, bool regroup, const ProblemK *d_probs,
+hipError_t launch_transport(bool fp32, bool batch, bool defer, int nl, bool regroup, const ProblemK *d_probs,
                             const int64_t *d_starts, int n_probs, unsigned long long *d_next, int refill_min,
                             int stack_levels, int grid, int block, void *slots, int budget,
                             unsigned long long *slice, hipStream_t st) {
-  hipLaunchKernelGGL(transport_fn(fp32, batch, defer, one_line, regroup), dim3(grid), dim3(block),
+  hipLaunchKernelGGL(transport_fn(fp32, batch, defer, nl, regroup), dim3(grid), dim3(block),
                      transport_lds(stack_levels, block), st,
                      d_probs, d_starts, n_probs, d_next, refill_min, stack_levels, (SlotState *)slots, budget, slice);
   return hipGetLastError();
 }
 
 template <class R>
-static void launch_walkers_as(bool batch, bool one_line, const ProblemK *d_probs, int region0, int levels,
+static void launch_walkers_as(bool batch, int nl, const ProblemK *d_probs, int region0, int levels,
                               SlotState *slots, int lp, int waves, int budget, unsigned long long *slice,
                               hipStream_t st) {
-  const auto fn = batch ? (one_line ? k_walkers<R, true, 1> : k_walkers<R, true, MAX_LINES>)
-                        : (one_line ? k_walkers<R, false, 1> : k_walkers<R, false, MAX_LINES>);
+  const auto fn = batch ? (nl == 1 ? k_walkers<R, true, 1> : nl == 2 ? k_walkers<R, true, 2> : k_walkers<R, true, MAX_LINES>)
+                        : (nl == 1   ? k_walkers<R, false, 1>
+                           : nl == 2 ? k_walkers<R, false, 2>
+                                     : k_walkers<R, false, MAX_LINES>);
   hipLaunchKernelGGL(fn, dim3(waves), dim3(64), (size_t)levels * 64 * sizeof(int), st, d_probs, region0, slots, lp,
                      budget, slice);
 }
 
-hipError_t launch_walkers(bool fp32, bool batch, bool one_line, const ProblemK *d_probs, int region0, int stack_levels,
+hipError_t launch_walkers(bool fp32, bool batch, int nl, const ProblemK *d_probs, int region0, int stack_levels,
                           void *slots, int lp, int waves, int budget, unsigned long long *slice, hipStream_t st) {
   SlotState *s = (SlotState *)slots;
-  if (fp32) launch_walkers_as<float>(batch, one_line, d_probs, region0, stack_levels, s, lp, waves, budget, slice, st);
-  else launch_walkers_as<double>(batch, one_line, d_probs, region0, stack_levels, s, lp, waves, budget, slice, st);
+  if (fp32) launch_walkers_as<float>(batch, nl, d_probs, region0, stack_levels, s, lp, waves, budget, slice, st);
+  else launch_walkers_as<double>(batch, nl, d_probs, region0, stack_levels, s, lp, waves, budget, slice, st);
   return hipGetLastError();
 }
 
@@ -2417,30 +2421,30 @@ hipError_t launch_group_slots(const void *src, int64_t n, void *dst, int64_t n_d
 using DrainFn = void (*)(const ProblemK *, PeelQueue *, unsigned long long *);
 
 template <class R>
-static DrainFn drain_fn(bool batch, bool one_line) {
-  if (batch) return one_line ? k_peel_drain<R, true, 1> : k_peel_drain<R, true, MAX_LINES>;
-  return one_line ? k_peel_drain<R, false, 1> : k_peel_drain<R, false, MAX_LINES>;
+static DrainFn drain_fn(bool batch, int nl) {
+  if (batch) return nl == 1 ? k_peel_drain<R, true, 1> : nl == 2 ? k_peel_drain<R, true, 2> : k_peel_drain<R, true, MAX_LINES>;
+  return nl == 1 ? k_peel_drain<R, false, 1> : nl == 2 ? k_peel_drain<R, false, 2> : k_peel_drain<R, false, MAX_LINES>;
 }
 
-static DrainFn drain_fn(bool fp32, bool batch, bool one_line) {
-  return fp32 ? drain_fn<float>(batch, one_line) : drain_fn<double>(batch, one_line);
+static DrainFn drain_fn(bool fp32, bool batch, int nl) {
+  return fp32 ? drain_fn<float>(batch, nl) : drain_fn<double>(batch, nl);
 }
 
-hipError_t launch_peel_drain(bool fp32, bool batch, bool one_line, const ProblemK *d_probs, void *pq,
+hipError_t launch_peel_drain(bool fp32, bool batch, int nl, const ProblemK *d_probs, void *pq,
                              int n_regions, int stack_levels, int grid, unsigned long long *slice, hipStream_t st) {
   const int b = 256;
   const size_t lds = (size_t)stack_levels * b * sizeof(int);
   PeelQueue *q = (PeelQueue *)pq;
   hipLaunchKernelGGL(k_peel_scan, dim3(1), dim3(1024), 0, st, q, n_regions, slice);
   if (hipError_t e = hipGetLastError()) return e;
-  hipLaunchKernelGGL(drain_fn(fp32, batch, one_line), dim3(grid), dim3(b), lds, st, d_probs, q, slice);
+  hipLaunchKernelGGL(drain_fn(fp32, batch, nl), dim3(grid), dim3(b), lds, st, d_probs, q, slice);
   return hipGetLastError();
 }
 
-int peel_drain_blocks_per_cu(bool fp32, bool batch, bool one_line, int stack_levels) {
+int peel_drain_blocks_per_cu(bool fp32, bool batch, int nl, int stack_levels) {
   const size_t lds = (size_t)stack_levels * 256 * sizeof(int);
   int nb = 0;
-  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, drain_fn(fp32, batch, one_line), 256, lds);
+  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, drain_fn(fp32, batch, nl), 256, lds);
   return (e == hipSuccess && nb > 0) ? nb : 1;
 }
 
@@ -2449,11 +2453,11 @@ size_t peel_queue_bytes() { return sizeof(PeelQueue); }
 
 size_t slot_bytes() { return sizeof(SlotState); }
 
-int transport_blocks_per_cu(bool fp32, bool batch, bool defer, bool one_line, bool regroup, int block,
+int transport_blocks_per_cu(bool fp32, bool batch, bool defer, int nl, bool regroup, int block,
                             int stack_levels) {
   int nb = 0;
   const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb,
-                                                                    transport_fn(fp32, batch, defer, one_line, regroup),
+                                                                    transport_fn(fp32, batch, defer, nl, regroup),
                                                                     block,
                                                                     transport_lds(stack_levels, block));
   return (e == hipSuccess && nb > 0) ? nb : 1;

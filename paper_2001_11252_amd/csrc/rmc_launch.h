@@ -8,18 +8,19 @@
 namespace rmc {
 
 // defer: peel-off rays past their first leaf go to the queue of
-// d_probs[0].pq (then launch_peel_drain must follow).  one_line: every
-// problem of the launch has a single line (a kernel specialised for it).
+// d_probs[0].pq (then launch_peel_drain must follow).  nl: the lines
+// the kernel is compiled for (1: every problem has a single line without
+// fluorescent channels; 2: at most two lines; MAX_LINES).
 // regroup (with defer): one rejection round of a line scattering per pass
 // of the loop, a rejected round leaving the event pending for the next.
-hipError_t launch_transport(bool fp32, bool batch, bool defer, bool one_line, bool regroup, const ProblemK *d_probs,
+hipError_t launch_transport(bool fp32, bool batch, bool defer, int nl, bool regroup, const ProblemK *d_probs,
                             const int64_t *d_starts, int n_probs, unsigned long long *d_next, int refill_min,
                             int stack_levels, int grid, int block, void *slots, int budget,
                             unsigned long long *slice, hipStream_t st);
 // The transport of the last packets (defer): `waves` waves of 2^lp slots each,
 // every wave's slots of one problem; no packet is taken from the queue.  Their
 // peel-off rays go to regions region0 .. region0 + waves - 1.
-hipError_t launch_walkers(bool fp32, bool batch, bool one_line, const ProblemK *d_probs, int region0, int stack_levels,
+hipError_t launch_walkers(bool fp32, bool batch, int nl, const ProblemK *d_probs, int region0, int stack_levels,
                           void *slots, int lp, int waves, int budget, unsigned long long *slice, hipStream_t st);
 // active slots of src[0, n) copied to dst[0, n_dst) (cleared), each of the
 // n_probs problems' in slots of its own, a multiple of 2^lp of them; work:
@@ -30,12 +31,12 @@ size_t slot_bytes();
 // Index of the jobs in the peel-off queue pq (a device PeelQueue) whose first
 // n_regions regions the last transport launch filled, then the ray-cast pass
 // over them; grid blocks of 256 threads.
-hipError_t launch_peel_drain(bool fp32, bool batch, bool one_line, const ProblemK *d_probs, void *pq,
+hipError_t launch_peel_drain(bool fp32, bool batch, int nl, const ProblemK *d_probs, void *pq,
                              int n_regions, int stack_levels, int grid, unsigned long long *slice, hipStream_t st);
-int peel_drain_blocks_per_cu(bool fp32, bool batch, bool one_line, int stack_levels);
+int peel_drain_blocks_per_cu(bool fp32, bool batch, int nl, int stack_levels);
 size_t peel_job_bytes(bool fp32);
 size_t peel_queue_bytes();
-int transport_blocks_per_cu(bool fp32, bool batch, bool defer, bool one_line, bool regroup, int block,
+int transport_blocks_per_cu(bool fp32, bool batch, bool defer, int nl, bool regroup, int block,
                             int stack_levels);
 hipError_t launch_clear_slots(void *slots, int64_t n, hipStream_t st);
 hipError_t launch_count_live(const void *slots, int64_t n, unsigned long long *out, hipStream_t st);
