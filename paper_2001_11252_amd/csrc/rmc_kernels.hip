@@ -1809,6 +1809,116 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DrainW
   if (lane == 0 && d) atomicAdd(slice + S_PEEL_DROPPED, d);
 }
 
+// --------------------------------------------------------- rays, leaf by leaf
+// A ray of fixed direction walked one leaf per step.  The next leaf's record is
+// asked for before the current one's opacity is computed: the geometry does not
+// depend on the record, so its load is hidden by that arithmetic (a ray is a
+// chain of dependent reads, and few rays leave nothing else to hide them).
+// Axes the direction does not move along are left out (for an observer along
+// an axis two of three; the tests are the same for every lane then), and the
+// distances are the correctly rounded quotients of exit_dist or, on the float
+// image path, its products with 1/k.
+// Measured, against walks without the early load, dividing and testing all
+// axes, with the lines in a loop: 4e6 FP32 rays of 30 crossings 1148 -> 935 us
+// (image), 1542 -> 1407 (image with crossing lists); 3e5 FP64 rays of 30 crossings
+// 238 -> 221 us (image), 704 -> 594 (adjoint); 20001 FP64 optical depths 458 -> 405 us
+// with their copies.
+template <class R, bool PRODUCT> struct RayWalk {
+  double p[3];
+  int X[3];
+  Cell c;
+  LeafRec<R> lf;
+
+  // The leaf of p; false outside the unit cube.
+  __device__ __forceinline__ bool start(const ProblemK &pb, const double k[3], int *stk, int stride) {
+    if (!int_coords(pb.L, p, k, X)) return false;
+    locate(pb, X, stk, stride, c);
+    lf = load_leaf<R>(pb.leaves, c.leaf);
+    return true;
+  }
+
+  // Leaves leaf *leaf (segment *seg, record *rec) for the next one; false when
+  // the ray ends at the domain border or leaves the cube.
+  __device__ __forceinline__ bool step(const ProblemK &pb, const double k[3], const double kinv[3], int *stk, int stride,
+                                       int *leaf, double *seg, LeafRec<R> *rec) {
+    const double inv = ldexp(1.0, -pb.L), sc = (double)(1 << pb.L);
+    const int side = 1 << pb.L, sz = 1 << (pb.L - c.level);
+    const int o[3] = {c.ox, c.oy, c.oz};
+    double lo[3], hi[3], t[3], te = __builtin_inf();
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      t[d] = __builtin_inf();
+      if (k[d] != 0.0) {
+        lo[d] = (double)o[d] * inv;
+        hi[d] = (double)(o[d] + sz) * inv;
+        const double a = (k[d] > 0.0 ? hi[d] : lo[d]) - p[d];
+        t[d] = PRODUCT ? a * kinv[d] : (fabs(k[d]) >= QUOTIENT_MIN ? quotient(a, k[d], kinv[d]) : a / k[d]);
+        te = t[d] < te ? t[d] : te;
+      }
+    }
+    te = te < 0.0 ? 0.0 : te;
+    double pn[3] = {p[0], p[1], p[2]};
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      if (k[d] != 0.0) {
+        const double q = fmin(fmax(fma(te, k[d], p[d]), lo[d]), hi[d]);
+        pn[d] = t[d] <= te ? (k[d] > 0.0 ? hi[d] : lo[d]) : q;
+      }
+    }
+    wrap_slab(pb.domain, pn, k);
+    bool in = true;
+    int Y[3] = {X[0], X[1], X[2]};
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      if (k[d] != 0.0) {
+        const double s = pn[d] * sc;
+        const double f = k[d] > 0.0 ? floor(s) : ceil(s) - 1.0;
+        const bool ok = f >= 0.0 && f < (double)side;
+        in = in && ok;
+        Y[d] = ok ? (int)f : 0;
+      }
+    }
+    *leaf = c.leaf;
+    *rec = lf;
+    const double td = domain_dist_leaf(lf, pb.domain, pb.dom, p, k);
+    *seg = td <= te ? td : te;
+    if (!in || td <= te) return false;
+    relocate(pb, Y, stk, stride, c);
+    lf = load_leaf<R>(pb.leaves, c.leaf);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      p[d] = pn[d];
+      X[d] = Y[d];
+    }
+    return true;
+  }
+};
+
+// Optical depth of the ray from p0 along k to the domain border; stops once
+// it reaches tau_cut.
+template <class R, int NL, bool PRODUCT>
+__device__ __forceinline__ double walk_tau(const ProblemK &pb, const double p0[3], const double k[3],
+                                           const double kinv[3], double x_ext, double tau_cut, int *stk, int stride,
+                                           uint32_t *ncross) {
+  const R kr[3] = {(R)k[0], (R)k[1], (R)k[2]};
+  RayWalk<R, PRODUCT> w;
+  w.p[0] = p0[0]; w.p[1] = p0[1]; w.p[2] = p0[2];
+  double tau = 0.0;
+  bool more = w.start(pb, k, stk, stride);
+  while (more) {
+    int leaf;
+    double seg;
+    LeafRec<R> rec;
+    more = w.step(pb, k, kinv, stk, stride, &leaf, &seg, &rec);
+    Opac<R, NL> o;
+    opacity(pb, rec, x_ext, kr, o);
+    tau += (double)o.ktot * seg;
+    ++*ncross;
+    if (tau >= tau_cut || *ncross >= MAX_CROSS) break;
+  }
+  return tau;
+}
+
 // ------------------------------------------------------------------ probes
 __global__ void k_trace(ProblemK pb, int64_t n, const double *__restrict__ orig,
                         const double *__restrict__ dir, int max_cells, int32_t *__restrict__ leaf_out,
@@ -1848,8 +1958,8 @@ __global__ void k_trace(ProblemK pb, int64_t n, const double *__restrict__ orig,
   n_out[r] = cnt;
 }
 
-template <class R>
-__global__ void k_tau(ProblemK pb, int64_t n, const double *__restrict__ orig,
+template <class R, int NL>
+__global__ void __launch_bounds__(256) k_tau(ProblemK pb, int64_t n, const double *__restrict__ orig,
                       const double *__restrict__ dir, const double *__restrict__ x_ext,
                       double *__restrict__ tau_out) {
   extern __shared__ int lds[];
@@ -1858,13 +1968,16 @@ __global__ void k_tau(ProblemK pb, int64_t n, const double *__restrict__ orig,
   if (r >= n) return;
   const double p[3] = {orig[3 * r], orig[3 * r + 1], orig[3 * r + 2]};
   const double k[3] = {dir[3 * r], dir[3 * r + 1], dir[3 * r + 2]};
+  double kinv[3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) kinv[d] = fabs(k[d]) >= QUOTIENT_MIN ? 1.0 / k[d] : 0.0;
   uint32_t nc = 0;
-  tau_out[r] = ray_tau<R>(pb, p, k, x_ext[r], __builtin_inf(), stk, blockDim.x, &nc, nullptr);
+  tau_out[r] = walk_tau<R, NL, false>(pb, p, k, kinv, x_ext[r], __builtin_inf(), stk, blockDim.x, &nc);
 }
 
 // ------------------------------------------------- peel-off image, adjoint
-template <class R>
-__global__ void k_image_fwd(ProblemK pb, int obs, int64_t n, const double *__restrict__ orig,
+template <class R, int NL>
+__global__ void __launch_bounds__(256) k_image_fwd(ProblemK pb, int obs, int64_t n, const double *__restrict__ orig,
                             const double *__restrict__ x_ext, const double *__restrict__ w,
                             double *__restrict__ image, unsigned long long *__restrict__ ncross) {
   extern __shared__ int lds[];
@@ -1876,8 +1989,8 @@ __global__ void k_image_fwd(ProblemK pb, int obs, int64_t n, const double *__res
     const double p[3] = {orig[3 * r], orig[3 * r + 1], orig[3 * r + 2]};
     const int pix = pixel_of(ob, p);
     if (pix >= 0) {
-      const double tau = ray_tau<R>(pb, p, ob.k, x_ext[r], TauCut<double>::v, stk, blockDim.x, &nc, nullptr,
-                                    sizeof(R) == 4 ? ob.kinv : nullptr);
+      const double tau = walk_tau<R, NL, sizeof(R) == 4>(pb, p, ob.k, ob.kinv, x_ext[r], TauCut<double>::v, stk,
+                                                         blockDim.x, &nc);
       if (tau < TauCut<double>::v) unsafeAtomicAdd(image + pix, w[r] * exp(-tau));
     }
   }
@@ -1887,31 +2000,54 @@ __global__ void k_image_fwd(ProblemK pb, int obs, int64_t n, const double *__res
   if (__lane_id() == 0 && v) atomicAdd(ncross, v);
 }
 
+// Sums of a, b and c over the wave, in the lanes of rows 0, 2 and 1 (lane >> 4;
+// row 3 holds 0): the three sums share their steps.  Halves are exchanged with
+// v_permlane32_swap, rows with v_permlane16_swap, lanes of a row by DPP, all
+// vector instructions, where butterflies through the LDS crossbar took 36
+// permutes a round (1.2e8 crossings of FP32 crossing lists: 1456 -> 1309 us).
+__device__ __forceinline__ double swap_add32(double x, double y) {
+  const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)__double2loint(x), (uint32_t)__double2loint(y), false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)__double2hiint(x), (uint32_t)__double2hiint(y), false, false);
+  return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+__device__ __forceinline__ double swap_add16(double x, double y) {
+  const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)__double2loint(x), (uint32_t)__double2loint(y), false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)__double2hiint(x), (uint32_t)__double2hiint(y), false, false);
+  return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+template <int CTRL> __device__ __forceinline__ double dpp_add(double x) {
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), CTRL, 0xf, 0xf, true);
+  return x + __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double wave_sum3(double a, double b, double c) {
+  // halves: the lower 32 lanes hold a (then c), the upper 32 b (then 0)
+  double s = swap_add16(swap_add32(a, b), swap_add32(c, 0.0));   // rows: a, c, b, 0
+  s = dpp_add<0x128>(s);   // row_ror 8, 4, 2, 1
+  s = dpp_add<0x124>(s);
+  s = dpp_add<0x122>(s);
+  return dpp_add<0x121>(s);
+}
+
 // Adds each lane's (an, ak, av) to leaf `leaf` (< 0: nothing) of the
 // gradients: one sum and one atomic per distinct leaf of the wave (a few
-// when a wave holds rays of two sources); lanes with many distinct leaves
-// fall back to their own atomics after four rounds.  Every lane of the
-// wave must call it (shuffles).
+// when a wave holds rays of two sources); lanes that share their leaf with few
+// others, and what is left after four rounds, add their own.  Every lane of the
+// wave must call it (cross-lane reads).
 __device__ __forceinline__ void wave_leaf_add(int leaf, double an, double ak, double av, double *g_n,
                                               double *g_k, double *g_v, int lane) {
   unsigned long long m = __ballot(leaf >= 0);
   for (int round = 0; m && round < 4; ++round) {
-    const int lead = __ffsll((long long)m) - 1;
-    const int l0 = __shfl(leaf, lead);
+    const int l0 = __builtin_amdgcn_readlane(leaf, __ffsll((long long)m) - 1);
     const bool mine = leaf == l0;
-    double sn = mine ? an : 0.0, sk = mine ? ak : 0.0, sv = mine ? av : 0.0;
-    for (int off = 32; off > 0; off >>= 1) {
-      sn += __shfl_xor(sn, off);
-      sk += __shfl_xor(sk, off);
-      sv += __shfl_xor(sv, off);
-    }
-    if (lane == lead) {
-      unsafeAtomicAdd(g_n + l0, sn);
-      unsafeAtomicAdd(g_k + l0, sk);
-      unsafeAtomicAdd(g_v + l0, sv);
-    }
+    const unsigned long long same = __ballot(mine);
+    // (four lanes' own atomics cost about what a sum over the wave does)
+    if (__popcll(same) < 4) break;
+    const double s = wave_sum3(mine ? an : 0.0, mine ? av : 0.0, mine ? ak : 0.0);
+    double *const g = lane == 0 ? g_n : (lane == 16 ? g_k : g_v);
+    if (lane == 0 || lane == 16 || lane == 32) unsafeAtomicAdd(g + l0, s);
     if (mine) leaf = -1;
-    m = __ballot(leaf >= 0);
+    m &= ~same;
   }
   if (leaf >= 0) {
     unsafeAtomicAdd(g_n + leaf, an);
@@ -1922,19 +2058,23 @@ __device__ __forceinline__ void wave_leaf_add(int leaf, double an, double ak, do
 
 // Gradient terms of one crossing (segment seg of leaf record lf) of a ray
 // at x_ext xr with weight g = -G_p w exp(-tau): d/dn_HI, d/dkappa_d and
-// d/dv_los of g tau_c (formulas below).
-template <class R>
+// d/dv_los of g tau_c (formulas below).  In float the loop over the lines is
+// kept as a loop at one line too: unrolled, the compiler fuses other products
+// and the sums move by 2e-8, more than their order alone does (1e-16).
+template <class R, int NL> constexpr int grad_lines() { return sizeof(R) == 4 ? MAX_LINES : NL; }
+
+template <class R, int NL>
 __device__ __forceinline__ void crossing_grad(const ProblemK &pb, const LeafRec<R> &lf, double xr, const R kr[3],
                                               double seg, double g, double inv_vth_ref, double *an, double *ak,
                                               double *av) {
-  Opac<R> o;
+  Opac<R, NL> o;
   opacity(pb, lf, xr, kr, o);
   const R b = R(pb.b_ref);
   const R den = R(1) + b * o.w;
   R sn = R(0), sv = R(0);
 #pragma unroll
-  for (int i = 0; i < MAX_LINES; ++i) {
-    if (i < pb.n_lines) {
+  for (int i = 0; i < NL; ++i) {
+    if (NL == 1 || i < pb.n_lines) {
       const LineK &ln = pb.lines[i];
       const R a = R(ln.alpha) * lf.irho;
       sn += R(ln.kfac) * voigt_h<R>(a, o.x[i]);
@@ -1953,7 +2093,7 @@ __device__ __forceinline__ void crossing_grad(const ProblemK &pb, const LeafRec<
 //   dtau/dkappa_d = seg box
 //   dtau/dv_los  = seg nl sum_i kfac_i H'_i dx_i/dw / v_th,ref,
 //   dx_i/dw = -irho inv_mu_i s_i (1 + b x_ext) / (1 + b w)^2.
-template <class R>
+template <class R, int NL>
 __global__ void __launch_bounds__(256) k_image_bwd(ProblemK pb, int obs, int64_t n, const double *__restrict__ orig,
                             const double *__restrict__ x_ext, const double *__restrict__ w,
                             const double *__restrict__ G, double inv_vth_ref,
@@ -1964,31 +2104,24 @@ __global__ void __launch_bounds__(256) k_image_bwd(ProblemK pb, int obs, int64_t
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int lane = __lane_id();
   uint32_t nc = 0;
-  const double *k = pb.obs[obs].k;
-  const R kr[3] = {(R)k[0], (R)k[1], (R)k[2]};
+  const ObsK &ob = pb.obs[obs];
+  const R kr[3] = {(R)ob.k[0], (R)ob.k[1], (R)ob.k[2]};
   bool walking = false;
   double g = 0.0, xr = 0.0;
-  double p[3] = {0.0, 0.0, 0.0};
-  Cell c;
+  RayWalk<R, sizeof(R) == 4> wk;
   uint32_t steps = 0;
   if (r < n) {
-    const ObsK &ob = pb.obs[obs];
     const double p0[3] = {orig[3 * r], orig[3 * r + 1], orig[3 * r + 2]};
     const int pix = pixel_of(ob, p0);
     xr = x_ext[r];
     double tau = TauCut<double>::v;
     if (pix >= 0)
-      tau = ray_tau<R>(pb, p0, ob.k, xr, TauCut<double>::v, stk, blockDim.x, &nc, nullptr,
-                       sizeof(R) == 4 ? ob.kinv : nullptr);
+      tau = walk_tau<R, NL, sizeof(R) == 4>(pb, p0, ob.k, ob.kinv, xr, TauCut<double>::v, stk, blockDim.x, &nc);
     g = (pix >= 0 && tau < TauCut<double>::v) ? -G[pix] * w[r] * exp(-tau) : 0.0;
     if (g != 0.0) {
       // replay the ray (same traversal as the forward pass)
-      p[0] = p0[0]; p[1] = p0[1]; p[2] = p0[2];
-      int X[3];
-      if (int_coords(pb.L, p, k, X)) {
-        locate(pb, X, stk, blockDim.x, c);
-        walking = true;
-      }
+      wk.p[0] = p0[0]; wk.p[1] = p0[1]; wk.p[2] = p0[2];
+      walking = wk.start(pb, ob.k, stk, blockDim.x);
     }
   }
   // The wave walks its rays in step (every lane runs every iteration) so
@@ -2000,29 +2133,11 @@ __global__ void __launch_bounds__(256) k_image_bwd(ProblemK pb, int obs, int64_t
     int leaf = -1;
     double an = 0.0, ak = 0.0, av = 0.0;
     if (walking) {
-      const LeafRec<R> lf = load_leaf<R>(pb.leaves, c.leaf);
-      double face[3], lo[3], hi[3];
-      int em;
-      const double te = exit_dist(c, pb.L, p, k, face, lo, hi, &em, sizeof(R) == 4 ? pb.obs[obs].kinv : nullptr);
-      const double td = domain_dist_leaf(lf, pb.domain, pb.dom, p, k);
-      const double seg = td <= te ? td : te;
-      crossing_grad<R>(pb, lf, xr, kr, seg, g, inv_vth_ref, &an, &ak, &av);
-      leaf = c.leaf;
-      if (td <= te) {
-        walking = false;
-      } else {
-        double pn[3];
-        exit_point(te, em, p, k, face, lo, hi, pn);
-        p[0] = pn[0]; p[1] = pn[1]; p[2] = pn[2];
-        wrap_slab(pb.domain, p, k);
-        int X[3];
-        if (!int_coords(pb.L, p, k, X)) {
-          walking = false;
-        } else {
-          relocate(pb, X, stk, blockDim.x, c);
-          if (++steps >= MAX_CROSS) walking = false;
-        }
-      }
+      double seg;
+      LeafRec<R> rec;
+      walking = wk.step(pb, ob.k, ob.kinv, stk, blockDim.x, &leaf, &seg, &rec);
+      crossing_grad<R, grad_lines<R, NL>()>(pb, rec, xr, kr, seg, g, inv_vth_ref, &an, &ak, &av);
+      if (++steps >= MAX_CROSS) walking = false;
     }
     wave_leaf_add(leaf, an, ak, av, g_n, g_k, g_v, lane);
   }
@@ -2037,9 +2152,9 @@ __global__ void __launch_bounds__(256) k_image_bwd(ProblemK pb, int obs, int64_t
 // chunk (one atomic) and links it to its last one.  A wave that finds no
 // chunk left goes on without recording (the host sees the count of chunks
 // requested exceed the capacity and runs the pass again with more).  The
-// walk and the optical depth are those of ray_tau, so the image equals the
+// walk and the optical depth are those of walk_tau, so the image equals the
 // one k_image_fwd makes, up to the order of the additions.
-template <class R>
+template <class R, int NL>
 __global__ void __launch_bounds__(256) k_image_fwd_tape(ProblemK pb, int obs, int64_t n,
                                                         const double *__restrict__ orig,
                                                         const double *__restrict__ x_ext,
@@ -2053,23 +2168,17 @@ __global__ void __launch_bounds__(256) k_image_fwd_tape(ProblemK pb, int obs, in
   const ObsK &ob = pb.obs[obs];
   const double *k = ob.k;
   const R kr[3] = {(R)k[0], (R)k[1], (R)k[2]};
-  const double *kinv = sizeof(R) == 4 ? ob.kinv : nullptr;
   const double cut = TauCut<double>::v;
   bool walking = false;
   int pix = -1;
   double xr = 0.0, tau = 0.0;
-  double p[3] = {0.0, 0.0, 0.0};
-  Cell c;
+  RayWalk<R, sizeof(R) == 4> wk;
   uint32_t nc = 0;
   if (r < n) {
-    p[0] = orig[3 * r]; p[1] = orig[3 * r + 1]; p[2] = orig[3 * r + 2];
-    pix = pixel_of(ob, p);
+    wk.p[0] = orig[3 * r]; wk.p[1] = orig[3 * r + 1]; wk.p[2] = orig[3 * r + 2];
+    pix = pixel_of(ob, wk.p);
     xr = x_ext[r];
-    int X[3];
-    if (pix >= 0 && int_coords(pb.L, p, k, X)) {
-      locate(pb, X, stk, blockDim.x, c);
-      walking = true;
-    }
+    walking = pix >= 0 && wk.start(pb, k, stk, blockDim.x);
   }
   if (lane == 0) tp.first[wave] = -1;
   int64_t chunk = -1;   // wave-uniform
@@ -2087,35 +2196,20 @@ __global__ void __launch_bounds__(256) k_image_fwd_tape(ProblemK pb, int obs, in
       chunk = nxt;
     }
     if (walking) {
-      const LeafRec<R> lf = load_leaf<R>(pb.leaves, c.leaf);
-      Opac<R> o;
-      opacity(pb, lf, xr, kr, o);
-      double face[3], lo[3], hi[3];
-      int em;
-      const double te = exit_dist(c, pb.L, p, k, face, lo, hi, &em, kinv);
-      const double td = domain_dist_leaf(lf, pb.domain, pb.dom, p, k);
-      const double seg = td <= te ? td : te;
-      ++nc;
+      int leaf;
+      double seg;
+      LeafRec<R> rec;
+      walking = wk.step(pb, k, ob.kinv, stk, blockDim.x, &leaf, &seg, &rec);
       if (chunk >= 0) {
         const size_t e = (size_t)chunk * TAPE_ENTRIES + (size_t)(i % TAPE_CHUNK) * 64 + lane;
-        tp.leaf[e] = c.leaf;
+        tp.leaf[e] = leaf;
         ((R *)tp.seg)[e] = (R)seg;
       }
+      Opac<R, NL> o;
+      opacity(pb, rec, xr, kr, o);
       tau += (double)o.ktot * seg;
-      if (td <= te || tau >= cut) {
-        walking = false;
-      } else {
-        double pn[3];
-        exit_point(te, em, p, k, face, lo, hi, pn);
-        p[0] = pn[0]; p[1] = pn[1]; p[2] = pn[2];
-        wrap_slab(pb.domain, p, k);
-        int X[3];
-        if (!int_coords(pb.L, p, k, X) || nc >= MAX_CROSS) {
-          walking = false;
-        } else {
-          relocate(pb, X, stk, blockDim.x, c);
-        }
-      }
+      ++nc;
+      if (tau >= cut || nc >= MAX_CROSS) walking = false;
     }
   }
   if (r < n) {
@@ -2136,7 +2230,7 @@ __global__ void __launch_bounds__(256) k_image_fwd_tape(ProblemK pb, int obs, in
 // the order they were walked, so no geometry and no optical depth are
 // computed again.  The gradient terms and their per-leaf wave sums are
 // those of k_image_bwd.
-template <class R>
+template <class R, int NL>
 __global__ void __launch_bounds__(256) k_image_bwd_tape(ProblemK pb, int obs, int64_t n, TapeK tp,
                                                         const double *__restrict__ G, double inv_vth_ref,
                                                         double *__restrict__ g_n, double *__restrict__ g_k,
@@ -2174,7 +2268,7 @@ __global__ void __launch_bounds__(256) k_image_bwd_tape(ProblemK pb, int obs, in
       leaf = tp.leaf[e];
       const double seg = (double)((const R *)tp.seg)[e];
       const LeafRec<R> lf = load_leaf<R>(pb.leaves, leaf);
-      crossing_grad<R>(pb, lf, xr, kr, seg, g, inv_vth_ref, &an, &ak, &av);
+      crossing_grad<R, grad_lines<R, NL>()>(pb, lf, xr, kr, seg, g, inv_vth_ref, &an, &ak, &av);
     }
     wave_leaf_add(leaf, an, ak, av, g_n, g_k, g_v, lane);
   }
@@ -2490,42 +2584,42 @@ hipError_t launch_trace(const ProblemK &pb, int64_t n, const double *orig, const
   return hipGetLastError();
 }
 
+// Threads per block of the ray kernels: one wave where blocks of four waves would
+// not give each of the 256 CUs one.  A ray is a serial chain, and single waves
+// spread over the CUs.  FP64 optical depths with their copies, blocks of 256 ->
+// of 64 threads: 5000 rays 400 -> 329 us, 20001 rays 436 -> 403; from 65536 rays
+// (525 and 524) to 1e6 both take the same within 2%.
+static int ray_block(int64_t n) { return n < 256 * 256 ? 64 : 256; }
+
 hipError_t launch_tau(bool fp32, const ProblemK &pb, int64_t n, const double *orig, const double *dir,
                       const double *x, double *tau, hipStream_t st) {
-  const int b = 256;
+  const int b = ray_block(n);
   const size_t lds = (size_t)(pb.L > 0 ? pb.L : 1) * b * sizeof(int);
-  if (fp32)
-    hipLaunchKernelGGL(k_tau<float>, dim3(blocks_for(n, b)), dim3(b), lds, st, pb, n, orig, dir, x, tau);
-  else
-    hipLaunchKernelGGL(k_tau<double>, dim3(blocks_for(n, b)), dim3(b), lds, st, pb, n, orig, dir, x, tau);
+  const auto fn = fp32 ? (pb.n_lines == 1 ? k_tau<float, 1> : k_tau<float, MAX_LINES>)
+                       : (pb.n_lines == 1 ? k_tau<double, 1> : k_tau<double, MAX_LINES>);
+  hipLaunchKernelGGL(fn, dim3(blocks_for(n, b)), dim3(b), lds, st, pb, n, orig, dir, x, tau);
   return hipGetLastError();
 }
 
 hipError_t launch_image_fwd(bool fp32, const ProblemK &pb, int obs, int64_t n, const double *orig,
                             const double *x, const double *w, double *image, unsigned long long *ncross,
                             hipStream_t st) {
-  const int b = 256;
+  const int b = ray_block(n);
   const size_t lds = (size_t)(pb.L > 0 ? pb.L : 1) * b * sizeof(int);
-  if (fp32)
-    hipLaunchKernelGGL(k_image_fwd<float>, dim3(blocks_for(n, b)), dim3(b), lds, st, pb, obs, n, orig, x, w,
-                       image, ncross);
-  else
-    hipLaunchKernelGGL(k_image_fwd<double>, dim3(blocks_for(n, b)), dim3(b), lds, st, pb, obs, n, orig, x, w,
-                       image, ncross);
+  const auto fn = fp32 ? (pb.n_lines == 1 ? k_image_fwd<float, 1> : k_image_fwd<float, MAX_LINES>)
+                       : (pb.n_lines == 1 ? k_image_fwd<double, 1> : k_image_fwd<double, MAX_LINES>);
+  hipLaunchKernelGGL(fn, dim3(blocks_for(n, b)), dim3(b), lds, st, pb, obs, n, orig, x, w, image, ncross);
   return hipGetLastError();
 }
 
 hipError_t launch_image_bwd(bool fp32, const ProblemK &pb, int obs, int64_t n, const double *orig,
                             const double *x, const double *w, const double *G, double inv_vth_ref,
                             double *gn, double *gk, double *gv, unsigned long long *ncross, hipStream_t st) {
-  const int b = 256;
+  const int b = ray_block(n);
   const size_t lds = (size_t)(pb.L > 0 ? pb.L : 1) * b * sizeof(int);
-  if (fp32)
-    hipLaunchKernelGGL(k_image_bwd<float>, dim3(blocks_for(n, b)), dim3(b), lds, st, pb, obs, n, orig, x, w, G,
-                       inv_vth_ref, gn, gk, gv, ncross);
-  else
-    hipLaunchKernelGGL(k_image_bwd<double>, dim3(blocks_for(n, b)), dim3(b), lds, st, pb, obs, n, orig, x, w, G,
-                       inv_vth_ref, gn, gk, gv, ncross);
+  const auto fn = fp32 ? (pb.n_lines == 1 ? k_image_bwd<float, 1> : k_image_bwd<float, MAX_LINES>)
+                       : (pb.n_lines == 1 ? k_image_bwd<double, 1> : k_image_bwd<double, MAX_LINES>);
+  hipLaunchKernelGGL(fn, dim3(blocks_for(n, b)), dim3(b), lds, st, pb, obs, n, orig, x, w, G, inv_vth_ref, gn, gk, gv, ncross);
   return hipGetLastError();
 }
 
@@ -2537,12 +2631,9 @@ hipError_t launch_image_fwd_tape(bool fp32, const ProblemK &pb, int obs, int64_t
   if (n <= 0) return hipSuccess;
   const int b = 256;
   const size_t lds = (size_t)(pb.L > 0 ? pb.L : 1) * b * sizeof(int);
-  if (fp32)
-    hipLaunchKernelGGL(k_image_fwd_tape<float>, dim3(blocks_for(n, b)), dim3(b), lds, st, pb, obs, n, orig, x, w,
-                       image, ncross, tp);
-  else
-    hipLaunchKernelGGL(k_image_fwd_tape<double>, dim3(blocks_for(n, b)), dim3(b), lds, st, pb, obs, n, orig, x, w,
-                       image, ncross, tp);
+  const auto fn = fp32 ? (pb.n_lines == 1 ? k_image_fwd_tape<float, 1> : k_image_fwd_tape<float, MAX_LINES>)
+                       : (pb.n_lines == 1 ? k_image_fwd_tape<double, 1> : k_image_fwd_tape<double, MAX_LINES>);
+  hipLaunchKernelGGL(fn, dim3(blocks_for(n, b)), dim3(b), lds, st, pb, obs, n, orig, x, w, image, ncross, tp);
   return hipGetLastError();
 }
 
@@ -2551,12 +2642,9 @@ hipError_t launch_image_bwd_tape(bool fp32, const ProblemK &pb, int obs, int64_t
                                  unsigned long long *ncross, hipStream_t st) {
   if (n <= 0) return hipSuccess;
   const int b = 256;
-  if (fp32)
-    hipLaunchKernelGGL(k_image_bwd_tape<float>, dim3(blocks_for(n, b)), dim3(b), 0, st, pb, obs, n, tp, G,
-                       inv_vth_ref, gn, gk, gv, ncross);
-  else
-    hipLaunchKernelGGL(k_image_bwd_tape<double>, dim3(blocks_for(n, b)), dim3(b), 0, st, pb, obs, n, tp, G,
-                       inv_vth_ref, gn, gk, gv, ncross);
+  const auto fn = fp32 ? (pb.n_lines == 1 ? k_image_bwd_tape<float, 1> : k_image_bwd_tape<float, MAX_LINES>)
+                       : (pb.n_lines == 1 ? k_image_bwd_tape<double, 1> : k_image_bwd_tape<double, MAX_LINES>);
+  hipLaunchKernelGGL(fn, dim3(blocks_for(n, b)), dim3(b), 0, st, pb, obs, n, tp, G, inv_vth_ref, gn, gk, gv, ncross);
   return hipGetLastError();
 }
 
