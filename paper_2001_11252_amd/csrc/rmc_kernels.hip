@@ -2379,14 +2379,41 @@ __global__ void k_vlos_to_v(int64_t n, const double *__restrict__ g_vlos, double
 #pragma clang fp contract(fast)
 
 // --------------------------------------------------------------- helpers
-__global__ void k_hist(int64_t n, const int32_t *__restrict__ status, const double *__restrict__ x,
-                       int nbins, double x_min, double span, unsigned long long *__restrict__ h) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n || status[i] != ST_ESCAPED) return;
-  const double fb = (x[i] - x_min) / span * nbins;
-  if (!(fb >= 0.0 && fb < nbins)) return;
+// The bin of packet i, or -1 (not escaped, or outside the range).
+__device__ __forceinline__ int hist_bin(int32_t status, double x, int nbins, double x_min, double span) {
+  const double fb = (x - x_min) / span * nbins;
+  if (status != ST_ESCAPED || !(fb >= 0.0 && fb < nbins)) return -1;
   const int b = (int)floor(fb);
-  if (b < nbins) atomicAdd(h + b, 1ull);
+  return b < nbins ? b : -1;
+}
+
+// Spectrum of escaped packets.  Most of them share a few hundred bins, and
+// atomics on one address wait for each other: each block counts its packets in
+// LDS and adds its non-zero bins.  2e6 packets in 700 bins: 28 us, with one atomic
+// a packet 980 us.
+__global__ void __launch_bounds__(256) k_hist(int64_t n, const int32_t *__restrict__ status,
+                                              const double *__restrict__ x, int nbins, double x_min, double span,
+                                              unsigned long long *__restrict__ h) {
+  extern __shared__ int lds[];
+  unsigned *const cnt = (unsigned *)lds;
+  for (int b = threadIdx.x; b < nbins; b += blockDim.x) cnt[b] = 0u;
+  __syncthreads();
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+    const int b = hist_bin(status[i], x[i], nbins, x_min, span);
+    if (b >= 0) atomicAdd(cnt + b, 1u);
+  }
+  __syncthreads();
+  for (int b = threadIdx.x; b < nbins; b += blockDim.x)
+    if (cnt[b]) atomicAdd(h + b, (unsigned long long)cnt[b]);
+}
+
+// The same with an atomic a packet, for more bins than a block's LDS holds.
+__global__ void k_hist_wide(int64_t n, const int32_t *__restrict__ status, const double *__restrict__ x, int nbins,
+                            double x_min, double span, unsigned long long *__restrict__ h) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const int b = hist_bin(status[i], x[i], nbins, x_min, span);
+  if (b >= 0) atomicAdd(h + b, 1ull);
 }
 
 // Zero the counters of every problem of a launch, the work queue and its
@@ -2686,10 +2713,22 @@ hipError_t launch_vlos_to_v(int64_t n, const double *g_vlos, const double k[3], 
   return hipGetLastError();
 }
 
+// Bins of a block's LDS counters (32 KB: four blocks a CU), and blocks of a
+// large launch: four a CU.
+constexpr int HIST_LDS_BINS = 8192;
+constexpr int HIST_BLOCKS = 1024;
+
 hipError_t launch_hist(int64_t n, const int32_t *status, const double *x, int nbins, double x_min, double span,
                        unsigned long long *h, hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_hist, dim3(blocks_for(n, 256)), dim3(256), 0, st, n, status, x, nbins, x_min, span, h);
+  // a block's 32-bit counts hold its share of the packets (n < 2^31)
+  if (nbins <= HIST_LDS_BINS && n < ((int64_t)1 << 31)) {
+    const int blocks = n < 256 * HIST_BLOCKS ? blocks_for(n, 256) : HIST_BLOCKS;
+    hipLaunchKernelGGL(k_hist, dim3(blocks), dim3(256), (size_t)nbins * sizeof(unsigned), st, n, status, x, nbins,
+                       x_min, span, h);
+  } else {
+    hipLaunchKernelGGL(k_hist_wide, dim3(blocks_for(n, 256)), dim3(256), 0, st, n, status, x, nbins, x_min, span, h);
+  }
   return hipGetLastError();
 }
 
