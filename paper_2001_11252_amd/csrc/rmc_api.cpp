@@ -170,6 +170,7 @@ struct rmc_ctx {
   int64_t tp_n = 0;
   uint64_t tp_gen = 0;
   int s_nl = 1;                      // lines the stream's kernels are compiled for (lines_for)
+  bool s_one = false;                // its ray-cast pass serves one observer of one problem
   bool s_defer = true;               // transport kernel without the inline peel-off walker
                                      // (deferred peel-off, or no observer in the stream)
   // deferred peel-off rays: control block (PeelQueue) and job buffer
@@ -1171,7 +1172,7 @@ rmc_status stream_graphs(rmc_ctx *c) {
   snprintf(key, sizeof key, "%p/%p/%p/%p/%p/%p/%d/%d/%d/%d/%d/%d/%d/%d/%d", (void *)c->s_probs, (void *)c->s_starts,
            c->slots.p, c->d_slice.p, c->d_next.p, (void *)pq, n_probs, c->s_grid, c->block, c->refill, c->s_levels,
            c->precision, c->slice_iters, (int)batch,
-           (int)c->regroup * 16 + c->s_nl * 2 + (int)c->s_defer);
+           (int)c->s_one * 32 + (int)c->regroup * 16 + c->s_nl * 2 + (int)c->s_defer);
   if (c->s_key != key || !c->s_graph) {
     for (hipGraphExec_t *ge : {&c->s_graph, &c->s_graph2})
       if (*ge) {
@@ -1193,9 +1194,9 @@ rmc_status stream_graphs(rmc_ctx *c) {
                                c->d_next.as<unsigned long long>(), c->refill, c->s_levels, c->s_grid, c->block,
                                c->slots.p, c->slice_iters, c->d_slice.as<unsigned long long>(), cap);
       } else {
-        const int grid = c->num_cus * peel_drain_blocks_per_cu(f32, batch, c->s_nl, c->s_levels);
+        const int grid = c->num_cus * peel_drain_blocks_per_cu(f32, batch, c->s_one, c->s_nl, c->s_levels);
         if (e == hipSuccess)
-          e = launch_peel_drain(f32, batch, c->s_nl, c->s_probs, pq, (int)(n_slots / 64), c->s_levels, grid,
+          e = launch_peel_drain(f32, batch, c->s_one, c->s_nl, c->s_probs, pq, (int)(n_slots / 64), c->s_levels, grid,
                                 c->d_slice.as<unsigned long long>(),
                                 cap);
       }
@@ -1310,8 +1311,8 @@ rmc_status stream_launch(rmc_ctx *c, int budget, bool start_walkers, rmc_run_sta
     }
     HIPCHK(c, hipEventRecord(c->ev1, c->stream));
     if (c->s_pq)
-      HIPCHK(c, launch_peel_drain(f32, c->s_batch, c->s_nl, c->s_probs, c->s_pq, regions, c->s_levels,
-                                  c->num_cus * peel_drain_blocks_per_cu(f32, c->s_batch, c->s_nl, c->s_levels),
+      HIPCHK(c, launch_peel_drain(f32, c->s_batch, c->s_one, c->s_nl, c->s_probs, c->s_pq, regions, c->s_levels,
+                                  c->num_cus * peel_drain_blocks_per_cu(f32, c->s_batch, c->s_one, c->s_nl, c->s_levels),
                                   d_slice, c->stream));
   }
   HIPCHK(c, hipEventRecord(c->ev2, c->stream));
@@ -1377,6 +1378,7 @@ rmc_status stream_begin_single(rmc_ctx *c, uint64_t seed, int64_t first, int64_t
   c->pb_host.pq = c->s_pq;
   c->pb_host.index = 0;
   c->s_nl = lines_for(c);
+  c->s_one = c->obs.size() == 1;
   c->starts_host[0] = 0;
   c->starts_host[1] = n;
   HIPCHK(c, c->d_prob.ensure(sizeof(ProblemK)));
@@ -1865,6 +1867,7 @@ rmc_status batch_open(rmc_ctx *const *P, int np, const uint64_t *seeds, const in
   if (!any_obs) c0->s_pq = nullptr;
   c0->s_defer = c0->s_pq != nullptr || !any_obs;
   c0->s_nl = 1;
+  c0->s_one = false;
   for (int i = 0; i < np; ++i) c0->s_nl = std::max(c0->s_nl, lines_for(P[i]));
   c0->b_host.resize(np);
   c0->b_starts_host.assign(np + 1, 0);

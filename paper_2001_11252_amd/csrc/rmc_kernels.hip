@@ -1613,202 +1613,6 @@ __device__ __forceinline__ uint32_t region_of(const uint32_t *__restrict__ offs,
   return lo;
 }
 
-// Ray-cast pass over the peel-off rays queued by a transport launch.  A
-// wave takes runs of queued jobs by their running index over all regions
-// (k_peel_scan), so the pass spreads over the chip also where a few waves
-// queued every ray, as at the end of a run (handing a wave a whole region
-// left a complete 2e5-packet run of the dusty sphere at tau0 = 5e3 with
-// 208 ms of this pass out of 340 ms; it now takes 172 ms in all); each lane
-// walks one ray a leaf per iteration and takes the run's next ray as soon as
-// its own is done, so the waves stay full while ray lengths vary.  The walk is the one
-// of ray_walk from the queued state (a ray's start, or where it left its
-// first leaf), and every deferred deposit is made here.
-#ifndef RMC_DRAIN_WAVES_F32
-#define RMC_DRAIN_WAVES_F32 4
-#endif
-#ifndef RMC_DRAIN_WAVES_F64
-#define RMC_DRAIN_WAVES_F64 3
-#endif
-template <class R> struct DrainWaves;
-template <> struct DrainWaves<float> { static constexpr int v = RMC_DRAIN_WAVES_F32; };
-template <> struct DrainWaves<double> { static constexpr int v = RMC_DRAIN_WAVES_F64; };
-
-template <class R, bool BATCH, int NL>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DrainWaves<R>::v)))
-    k_peel_drain(const ProblemK *__restrict__ probs, PeelQueue *pq,
-                                                    unsigned long long *__restrict__ slice) {
-  extern __shared__ int lds[];
-  const int stride = blockDim.x;
-  int *stk = lds + threadIdx.x;
-  const int lane = __lane_id();
-  const unsigned long long cap = pq->cap;
-  const uint32_t n_regions = (uint32_t)pq->n_regions;
-  const PeelJob<R> *__restrict__ jobs = (const PeelJob<R> *)pq->jobs;
-  const uint32_t *__restrict__ offs = pq->offs;
-  const uint32_t total = offs[n_regions];
-  // jobs a wave takes at once: enough to spread what the take and its
-  // region search cost, few enough that the waves end together
-  const uint32_t share = total / (gridDim.x * (blockDim.x / 64) * 8u);
-  const uint32_t run = share < 64u ? 64u : (share > 1024u ? 1024u : share);
-  const double cut = TauCut<R>::v;
-  // wave-uniform: next job and end of the wave's run (its first one by its
-  // index, the next ones from pq->take), the region of the next job, its first
-  // job and its end (running indices)
-  const uint32_t wave = (uint32_t)blockIdx.x * (blockDim.x / 64) + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const uint32_t waves = gridDim.x * (blockDim.x / 64);
-  if ((unsigned long long)wave * run >= total) return;
-  uint32_t cur = wave * run, end = total - cur < run ? total : cur + run, reg = 0, r_beg = 0, r_end = 0;
-  bool drained = false;
-  bool active = false;
-  int prob = 0, acc_prob = 0;
-  double p[3], k[3], tau = 0.0, x = 0.0;
-  R weight = R(0), kr[3];
-  unsigned long long elem = 0;
-  int oi = 0;
-  uint32_t steps = 0;
-  Cell c;
-  unsigned long long nc_prob = 0, nc_all = 0;
-  unsigned long long nd_prob = 0, nd_all = 0;   // float jobs outside the cube
-  while (true) {
-    unsigned long long idle = __ballot(!active);
-    while (idle && !drained) {
-      if (cur >= end) {
-        unsigned long long t = 0;
-        if (lane == 0) t = atomicAdd(&pq->take, (unsigned long long)run);
-        t = __shfl(t, 0) + (unsigned long long)waves * run;
-        if (t >= total) {
-          drained = true;
-          break;
-        }
-        cur = (uint32_t)t;
-        end = total - cur < run ? total : cur + run;
-        r_end = 0;
-      }
-      if (cur >= r_end) {
-        reg = region_of(offs, n_regions, cur, lane);
-        r_beg = offs[reg];
-        r_end = offs[reg + 1];
-      }
-      const uint32_t avail = (end < r_end ? end : r_end) - cur;
-      const uint32_t rank = (uint32_t)__popcll(idle & ((1ull << lane) - 1ull));
-      const bool mine = ((idle >> lane) & 1ull) && rank < avail;
-      if (mine) {
-        const PeelJob<R> j = jobs[reg * cap + (cur - r_beg) + rank];
-        const int jp = BATCH ? (int)(j.dst >> PQ_PROB_SHIFT) : 0;
-        if (BATCH && jp != acc_prob) {
-          if (nc_prob) atomicAdd(probs[acc_prob].stats + S_PEEL_CROSS, nc_prob);
-          if (nd_prob) atomicAdd(probs[acc_prob].stats + S_PEEL_DROPPED, nd_prob);
-          nc_prob = 0;
-          nd_prob = 0;
-          acc_prob = jp;
-        }
-        prob = jp;
-        const ProblemK &pb = probs[prob];
-        oi = (int)((j.dst >> PQ_OBS_SHIFT) & 15ull);
-        const ObsK &ob = pb.obs[oi];
-        k[0] = ob.k[0]; k[1] = ob.k[1]; k[2] = ob.k[2];
-        kr[0] = (R)k[0]; kr[1] = (R)k[1]; kr[2] = (R)k[2];
-        p[0] = j.p[0]; p[1] = j.p[1]; p[2] = j.p[2];
-        x = (double)j.x;
-        weight = (R)j.weight;
-        bool binned = true;
-        if constexpr (sizeof(R) == 8) {
-          tau = j.tau;
-          steps = j.steps;
-          elem = j.dst & PQ_ELEM_MASK;
-        } else {
-          // float jobs come unbinned, from the ray's start
-          tau = 0.0;
-          steps = 0;
-          const int pix = pixel_of<true>(ob, p);
-          const int bin = bin_of<true>(ob, x);
-          binned = pix >= 0 && bin >= 0;
-          elem = binned ? (unsigned long long)pix * ob.nbins + bin : 0ull;
-          if (!binned) {
-            ++nd_prob;
-            ++nd_all;
-          }
-        }
-        int X[3];
-        if (binned) {
-          if (steps < MAX_CROSS && int_coords(pb.L, p, k, X)) {
-            locate(pb, X, stk, stride, c);
-            active = true;
-          } else if (tau < cut) {
-            atomic_add_real((R *)ob.cube + elem, weight * M<R>::exp((R)(-tau)));
-          }
-        }
-      }
-      const uint32_t n_idle = (uint32_t)__popcll(idle);
-      cur += avail < n_idle ? avail : n_idle;
-      // lanes given a job that ended at once stay idle until the next pass
-      idle &= ~__ballot(mine);
-    }
-    if (__ballot(active) == 0ull) {
-      if (drained) break;
-      continue;
-    }
-    if (!active) continue;
-    const ProblemK &pb = probs[BATCH ? prob : 0];
-    const LeafRec<R> lf = load_leaf<R>(pb.leaves, c.leaf);
-    Opac<R, NL> o;
-    opacity(pb, lf, x, kr, o);
-    double face[3], lo[3], hi[3];
-    int em;
-    const double te = exit_dist(c, pb.L, p, k, face, lo, hi, &em, sizeof(R) == 4 ? pb.obs[oi].kinv : nullptr);
-    const double td = domain_dist_leaf(lf, pb.domain, pb.dom, p, k);
-    ++nc_prob;
-    ++nc_all;
-    bool done = false;
-    if (td <= te) {
-      tau += (double)o.ktot * td;
-      done = true;
-    } else {
-      tau += (double)o.ktot * te;
-      if (tau >= cut) {
-        done = true;
-      } else {
-        double pn[3];
-        exit_point(te, em, p, k, face, lo, hi, pn);
-        p[0] = pn[0]; p[1] = pn[1]; p[2] = pn[2];
-        wrap_slab(pb.domain, p, k);
-        int X[3];
-        if (!int_coords(pb.L, p, k, X)) {
-          done = true;
-        } else {
-          relocate(pb, X, stk, stride, c);
-          if (++steps >= MAX_CROSS) done = true;
-        }
-      }
-    }
-    if (done) {
-      if (tau < cut) atomic_add_real((R *)pb.obs[oi].cube + elem, weight * M<R>::exp((R)(-tau)));
-      active = false;
-    }
-  }
-  // crossings and dropped deposits: per problem, and for the launch's
-  // slice counters
-  if (BATCH) {
-    if (nc_prob) atomicAdd(probs[acc_prob].stats + S_PEEL_CROSS, nc_prob);
-    if (nd_prob) atomicAdd(probs[acc_prob].stats + S_PEEL_DROPPED, nd_prob);
-  } else {
-    unsigned long long v = nc_prob, d = nd_prob;
-    for (int off = 32; off > 0; off >>= 1) {
-      v += __shfl_down(v, off);
-      d += __shfl_down(d, off);
-    }
-    if (lane == 0 && v) atomicAdd(probs[0].stats + S_PEEL_CROSS, v);
-    if (lane == 0 && d) atomicAdd(probs[0].stats + S_PEEL_DROPPED, d);
-  }
-  unsigned long long v = nc_all, d = nd_all;
-  for (int off = 32; off > 0; off >>= 1) {
-    v += __shfl_down(v, off);
-    d += __shfl_down(d, off);
-  }
-  if (lane == 0 && v) atomicAdd(slice + S_PEEL_CROSS, v);
-  if (lane == 0 && d) atomicAdd(slice + S_PEEL_DROPPED, d);
-}
-
 // --------------------------------------------------------- rays, leaf by leaf
 // A ray of fixed direction walked one leaf per step.  The next leaf's record is
 // asked for before the current one's opacity is computed: the geometry does not
@@ -1830,7 +1634,8 @@ template <class R, bool PRODUCT> struct RayWalk {
   LeafRec<R> lf;
 
   // The leaf of p; false outside the unit cube.
-  __device__ __forceinline__ bool start(const ProblemK &pb, const double k[3], int *stk, int stride) {
+  template <class PB>
+  __device__ __forceinline__ bool start(const PB &pb, const double k[3], int *stk, int stride) {
     if (!int_coords(pb.L, p, k, X)) return false;
     locate(pb, X, stk, stride, c);
     lf = load_leaf<R>(pb.leaves, c.leaf);
@@ -1839,7 +1644,8 @@ template <class R, bool PRODUCT> struct RayWalk {
 
   // Leaves leaf *leaf (segment *seg, record *rec) for the next one; false when
   // the ray ends at the domain border or leaves the cube.
-  __device__ __forceinline__ bool step(const ProblemK &pb, const double k[3], const double kinv[3], int *stk, int stride,
+  template <class PB>
+  __device__ __forceinline__ bool step(const PB &pb, const double k[3], const double kinv[3], int *stk, int stride,
                                        int *leaf, double *seg, LeafRec<R> *rec) {
     const double inv = ldexp(1.0, -pb.L), sc = (double)(1 << pb.L);
     const int side = 1 << pb.L, sz = 1 << (pb.L - c.level);
@@ -1894,6 +1700,202 @@ template <class R, bool PRODUCT> struct RayWalk {
   }
 };
 
+// Ray-cast pass over the peel-off rays queued by a transport launch.  A
+// wave takes runs of queued jobs by their running index over all regions
+// (k_peel_scan), so the pass spreads over the chip also where a few waves
+// queued every ray, as at the end of a run (handing a wave a whole region
+// left a complete 2e5-packet run of the dusty sphere at tau0 = 5e3 with
+// 208 ms of this pass, now 42); each lane
+// walks one ray a leaf per iteration and takes the run's next ray as soon as
+// its own is done, so the waves stay full while ray lengths vary.  The walk starts from
+// the queued state (a ray's start, or where it left its first leaf), and every
+// deferred deposit is made here.
+// Bound by the latency of its loads with four waves on a SIMD (vector
+// instructions take half the cycles; five waves spill).  RayWalk's early load
+// and a problem kept in registers gave 2%.  ONE, for a run of one problem and one
+// observer: the direction is the launch's, so it stays in scalar registers, and
+// the axes it does not move along cost nothing.  The pass in ms, general ->
+// ONE: dusty sphere 5e5 FP32 packets 16.5 -> 13.0, 2e5 to their end 42.0 -> 32.0,
+// H + D 18 -> 12.7, 1.5e5 FP64 packets 4.45 -> 4.13.
+#ifndef RMC_DRAIN_WAVES_F32
+#define RMC_DRAIN_WAVES_F32 4
+#endif
+#ifndef RMC_DRAIN_WAVES_F64
+#define RMC_DRAIN_WAVES_F64 3
+#endif
+template <class R> struct DrainWaves;
+template <> struct DrainWaves<float> { static constexpr int v = RMC_DRAIN_WAVES_F32; };
+template <> struct DrainWaves<double> { static constexpr int v = RMC_DRAIN_WAVES_F64; };
+
+template <class R, bool BATCH, bool ONE, int NL>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DrainWaves<R>::v)))
+    k_peel_drain(const ProblemK *__restrict__ probs, PeelQueue *pq,
+                                                    unsigned long long *__restrict__ slice) {
+  extern __shared__ int lds[];
+  const int stride = blockDim.x;
+  int *stk = lds + threadIdx.x;
+  const int lane = __lane_id();
+  const unsigned long long cap = pq->cap;
+  const uint32_t n_regions = (uint32_t)pq->n_regions;
+  const PeelJob<R> *__restrict__ jobs = (const PeelJob<R> *)pq->jobs;
+  const uint32_t *__restrict__ offs = pq->offs;
+  const uint32_t total = offs[n_regions];
+  // jobs a wave takes at once: enough to spread what the take and its
+  // region search cost, few enough that the waves end together
+  const uint32_t share = total / (gridDim.x * (blockDim.x / 64) * 8u);
+  const uint32_t run = share < 64u ? 64u : (share > 1024u ? 1024u : share);
+  const double cut = TauCut<R>::v;
+  // wave-uniform: next job and end of the wave's run (its first one by its
+  // index, the next ones from pq->take), the region of the next job, its first
+  // job and its end (running indices)
+  const uint32_t wave = (uint32_t)blockIdx.x * (blockDim.x / 64) + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint32_t waves = gridDim.x * (blockDim.x / 64);
+  if ((unsigned long long)wave * run >= total) return;
+  uint32_t cur = wave * run, end = total - cur < run ? total : cur + run, reg = 0, r_beg = 0, r_end = 0;
+  bool drained = false;
+  bool active = false;
+  int prob = 0, acc_prob = 0;
+  const WalkK<NL> one(probs[0], nullptr);   // the problem of a run without a batch, in registers
+  double k[3], kinv[3], tau = 0.0, x = 0.0;
+  R weight = R(0), kr[3];
+  if constexpr (ONE) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      k[d] = probs[0].obs[0].k[d];
+      kinv[d] = probs[0].obs[0].kinv[d];
+      kr[d] = (R)k[d];
+    }
+  }
+  unsigned long long elem = 0;
+  int oi = 0;
+  uint32_t steps = 0;
+  RayWalk<R, sizeof(R) == 4> wk;
+  unsigned long long nc_prob = 0, nc_all = 0;
+  unsigned long long nd_prob = 0, nd_all = 0;   // float jobs outside the cube
+  while (true) {
+    unsigned long long idle = __ballot(!active);
+    while (idle && !drained) {
+      if (cur >= end) {
+        unsigned long long t = 0;
+        if (lane == 0) t = atomicAdd(&pq->take, (unsigned long long)run);
+        t = __shfl(t, 0) + (unsigned long long)waves * run;
+        if (t >= total) {
+          drained = true;
+          break;
+        }
+        cur = (uint32_t)t;
+        end = total - cur < run ? total : cur + run;
+        r_end = 0;
+      }
+      if (cur >= r_end) {
+        reg = region_of(offs, n_regions, cur, lane);
+        r_beg = offs[reg];
+        r_end = offs[reg + 1];
+      }
+      const uint32_t avail = (end < r_end ? end : r_end) - cur;
+      const uint32_t rank = (uint32_t)__popcll(idle & ((1ull << lane) - 1ull));
+      const bool mine = ((idle >> lane) & 1ull) && rank < avail;
+      if (mine) {
+        const PeelJob<R> j = jobs[reg * cap + (cur - r_beg) + rank];
+        const int jp = BATCH ? (int)(j.dst >> PQ_PROB_SHIFT) : 0;
+        if (BATCH && jp != acc_prob) {
+          if (nc_prob) atomicAdd(probs[acc_prob].stats + S_PEEL_CROSS, nc_prob);
+          if (nd_prob) atomicAdd(probs[acc_prob].stats + S_PEEL_DROPPED, nd_prob);
+          nc_prob = 0;
+          nd_prob = 0;
+          acc_prob = jp;
+        }
+        prob = jp;
+        const ProblemK &pb = probs[prob];
+        oi = ONE ? 0 : (int)((j.dst >> PQ_OBS_SHIFT) & 15ull);
+        const ObsK &ob = pb.obs[oi];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+          wk.p[d] = j.p[d];
+          if constexpr (!ONE) {
+            k[d] = ob.k[d];
+            kinv[d] = ob.kinv[d];
+            kr[d] = (R)k[d];
+          }
+        }
+        x = (double)j.x;
+        weight = (R)j.weight;
+        bool binned = true;
+        if constexpr (sizeof(R) == 8) {
+          tau = j.tau;
+          steps = j.steps;
+          elem = j.dst & PQ_ELEM_MASK;
+        } else {
+          // float jobs come unbinned, from the ray's start
+          tau = 0.0;
+          steps = 0;
+          const int pix = pixel_of<true>(ob, wk.p);
+          const int bin = bin_of<true>(ob, x);
+          binned = pix >= 0 && bin >= 0;
+          elem = binned ? (unsigned long long)pix * ob.nbins + bin : 0ull;
+          if (!binned) {
+            ++nd_prob;
+            ++nd_all;
+          }
+        }
+        if (binned) {
+          if (steps < MAX_CROSS) active = BATCH ? wk.start(pb, k, stk, stride) : wk.start(one, k, stk, stride);
+          if (!active && tau < cut)
+            atomic_add_real((R *)ob.cube + elem, weight * M<R>::exp((R)(-tau)));
+        }
+      }
+      const uint32_t n_idle = (uint32_t)__popcll(idle);
+      cur += avail < n_idle ? avail : n_idle;
+      // lanes given a job that ended at once stay idle until the next pass
+      idle &= ~__ballot(mine);
+    }
+    if (__ballot(active) == 0ull) {
+      if (drained) break;
+      continue;
+    }
+    if (!active) continue;
+    int leaf;
+    double seg;
+    LeafRec<R> lf;
+    Opac<R, NL> o;
+    if constexpr (BATCH) {
+      active = wk.step(probs[prob], k, kinv, stk, stride, &leaf, &seg, &lf);
+      opacity(probs[prob], lf, x, kr, o);
+    } else {
+      active = wk.step(one, k, kinv, stk, stride, &leaf, &seg, &lf);
+      opacity(one, lf, x, kr, o);
+    }
+    ++nc_prob;
+    ++nc_all;
+    tau += (double)o.ktot * seg;
+    if (tau >= cut || ++steps >= MAX_CROSS) active = false;
+    if (!active && tau < cut)
+      atomic_add_real((R *)probs[prob].obs[oi].cube + elem, weight * M<R>::exp((R)(-tau)));
+  }
+  // crossings and dropped deposits: per problem, and for the launch's
+  // slice counters
+  if (BATCH) {
+    if (nc_prob) atomicAdd(probs[acc_prob].stats + S_PEEL_CROSS, nc_prob);
+    if (nd_prob) atomicAdd(probs[acc_prob].stats + S_PEEL_DROPPED, nd_prob);
+  } else {
+    unsigned long long v = nc_prob, d = nd_prob;
+    for (int off = 32; off > 0; off >>= 1) {
+      v += __shfl_down(v, off);
+      d += __shfl_down(d, off);
+    }
+    if (lane == 0 && v) atomicAdd(probs[0].stats + S_PEEL_CROSS, v);
+    if (lane == 0 && d) atomicAdd(probs[0].stats + S_PEEL_DROPPED, d);
+  }
+  unsigned long long v = nc_all, d = nd_all;
+  for (int off = 32; off > 0; off >>= 1) {
+    v += __shfl_down(v, off);
+    d += __shfl_down(d, off);
+  }
+  if (lane == 0 && v) atomicAdd(slice + S_PEEL_CROSS, v);
+  if (lane == 0 && d) atomicAdd(slice + S_PEEL_DROPPED, d);
+}
+
+// ---------------------------------------------------------- optical depths
 // Optical depth of the ray from p0 along k to the domain border; stops once
 // it reaches tau_cut.
 template <class R, int NL, bool PRODUCT>
@@ -2541,31 +2543,32 @@ hipError_t launch_group_slots(const void *src, int64_t n, void *dst, int64_t n_d
 
 using DrainFn = void (*)(const ProblemK *, PeelQueue *, unsigned long long *);
 
-template <class R>
-static DrainFn drain_fn(bool batch, int nl) {
-  if (batch) return nl == 1 ? k_peel_drain<R, true, 1> : nl == 2 ? k_peel_drain<R, true, 2> : k_peel_drain<R, true, MAX_LINES>;
-  return nl == 1 ? k_peel_drain<R, false, 1> : nl == 2 ? k_peel_drain<R, false, 2> : k_peel_drain<R, false, MAX_LINES>;
+template <class R, int NL>
+static DrainFn drain_fn(bool batch, bool one) {
+  return batch ? k_peel_drain<R, true, false, NL> : one ? k_peel_drain<R, false, true, NL> : k_peel_drain<R, false, false, NL>;
 }
 
-static DrainFn drain_fn(bool fp32, bool batch, int nl) {
-  return fp32 ? drain_fn<float>(batch, nl) : drain_fn<double>(batch, nl);
+static DrainFn drain_fn(bool fp32, bool batch, bool one, int nl) {
+  if (nl == 1) return fp32 ? drain_fn<float, 1>(batch, one) : drain_fn<double, 1>(batch, one);
+  if (nl == 2) return fp32 ? drain_fn<float, 2>(batch, one) : drain_fn<double, 2>(batch, one);
+  return fp32 ? drain_fn<float, MAX_LINES>(batch, one) : drain_fn<double, MAX_LINES>(batch, one);
 }
 
-hipError_t launch_peel_drain(bool fp32, bool batch, int nl, const ProblemK *d_probs, void *pq,
+hipError_t launch_peel_drain(bool fp32, bool batch, bool one, int nl, const ProblemK *d_probs, void *pq,
                              int n_regions, int stack_levels, int grid, unsigned long long *slice, hipStream_t st) {
   const int b = 256;
   const size_t lds = (size_t)stack_levels * b * sizeof(int);
   PeelQueue *q = (PeelQueue *)pq;
   hipLaunchKernelGGL(k_peel_scan, dim3(1), dim3(1024), 0, st, q, n_regions, slice);
   if (hipError_t e = hipGetLastError()) return e;
-  hipLaunchKernelGGL(drain_fn(fp32, batch, nl), dim3(grid), dim3(b), lds, st, d_probs, q, slice);
+  hipLaunchKernelGGL(drain_fn(fp32, batch, one, nl), dim3(grid), dim3(b), lds, st, d_probs, q, slice);
   return hipGetLastError();
 }
 
-int peel_drain_blocks_per_cu(bool fp32, bool batch, int nl, int stack_levels) {
+int peel_drain_blocks_per_cu(bool fp32, bool batch, bool one, int nl, int stack_levels) {
   const size_t lds = (size_t)stack_levels * 256 * sizeof(int);
   int nb = 0;
-  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, drain_fn(fp32, batch, nl), 256, lds);
+  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, drain_fn(fp32, batch, one, nl), 256, lds);
   return (e == hipSuccess && nb > 0) ? nb : 1;
 }
 

@@ -30,10 +30,11 @@ hipError_t launch_group_slots(const void *src, int64_t n, void *dst, int64_t n_d
 size_t slot_bytes();
 // Index of the jobs in the peel-off queue pq (a device PeelQueue) whose first
 // n_regions regions the last transport launch filled, then the ray-cast pass
-// over them; grid blocks of 256 threads.
-hipError_t launch_peel_drain(bool fp32, bool batch, int nl, const ProblemK *d_probs, void *pq,
+// over them; grid blocks of 256 threads.  one: a single problem with a single
+// observer.
+hipError_t launch_peel_drain(bool fp32, bool batch, bool one, int nl, const ProblemK *d_probs, void *pq,
                              int n_regions, int stack_levels, int grid, unsigned long long *slice, hipStream_t st);
-int peel_drain_blocks_per_cu(bool fp32, bool batch, int nl, int stack_levels);
+int peel_drain_blocks_per_cu(bool fp32, bool batch, bool one, int nl, int stack_levels);
 size_t peel_job_bytes(bool fp32);
 size_t peel_queue_bytes();
 int transport_blocks_per_cu(bool fp32, bool batch, bool defer, int nl, bool regroup, int block,
