@@ -1111,10 +1111,12 @@ rmc_status grow_queue(rmc_ctx *c, unsigned long long max_region) {
 // 4834 / 4854 on 512 and 6564 / 5839 on 1024; at 4096 packets (16 a wave on
 // 256) 5287 / 5920 against 5628 / 4803 on 1024, and beyond that the more waves
 // the faster.  k_transport took 7118 / 9122 at 1024 packets.
+// FP32 stops at 32 a wave: with 64 a step of 65536 packets with peel-off takes 12440
+// cycles, k_transport 10800 (FP64 22700 against 25600).
 int walker_waves(const rmc_ctx *c, int64_t live, int n_probs, int *lp) {
   const int64_t extra = std::min<int64_t>(n_probs - 1, live);   // each problem's last wave may be partly filled
   for (const int64_t most : {(int64_t)c->num_cus, (int64_t)c->num_cus * 4}) {
-    for (int l = 0; l <= (most == c->num_cus ? 3 : 6); ++l) {
+    for (int l = 0; l <= (most == c->num_cus ? 3 : c->precision == RMC_FP32_BULK ? 5 : 6); ++l) {
       const int64_t w = ((live + (1 << l) - 1) >> l) + extra;
       if (w <= most) {
         *lp = l;
@@ -1352,7 +1354,12 @@ rmc_status stream_step(rmc_ctx *c, rmc_run_stats *slice, int64_t *remaining) {
   const bool start_walkers = c->s_started == 0 && c->compact && c->s_defer && c->slice_iters > 1 &&
                              (int64_t)c->s_grid * c->block >= c->s_total &&
                              walker_waves(c, c->s_total, c->s_nprobs, &lp) > 0;
-  rmc_status r = stream_launch(c, c->slice_iters, start_walkers, &z);
+  // Gathered slots that are too many for the walkers run half a slice: those
+  // near their end leave few enough for them (1.5e5 FP64 packets of 2000 events, first
+  // run of a context, whose launches the queue's growth shifts: 56 ms with whole
+  // slices, 50.5 with halves; an eighth cost the FP32 spheres 2%).
+  const int budget = c->s_tail_grid > 0 ? std::max(c->slice_iters / 2, 1) : c->slice_iters;
+  rmc_status r = stream_launch(c, budget, start_walkers, &z);
   if (r) return r;
   add_run_stats(c->s_acc, z);
   if (slice) *slice = z;
