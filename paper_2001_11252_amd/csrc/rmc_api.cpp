@@ -1032,7 +1032,13 @@ void add_run_stats(rmc_run_stats &a, const rmc_run_stats &b) {
 }
 
 constexpr unsigned long long PQ_FIRST_CAP = 1024;          // jobs per region (one region per wave)
-constexpr unsigned long long PQ_MAX_BYTES = 32ull << 30;    // job buffer limit
+// Job buffer limit: room for half a slice's rays of a full grid of FP32 waves
+// and one observer.  Larger buffers save nothing (a slice cut in two costs a
+// launch), but once written they are slow to give back: with 32 GiB the second and
+// later contexts' first runs of the dusty sphere (2e5 packets) took 339 ms and their
+// closing 620-660, now 116 and 2.5; repeated runs take 111 either way (10 GiB 113,
+// 4 GiB 116).
+constexpr unsigned long long PQ_MAX_BYTES = 11ull << 30;
 static_assert(PQ_FIRST_CAP > 2 * 64 * MAX_OBS, "a region must hold one wave iteration of pushes");
 
 // Control block of the deferred peel-off queue, or null when peel-off rays
