@@ -68,7 +68,8 @@ enum {
   RMC_OPT_PEEL_DEFER = 6,    /* 1 (default): a peel-off ray whose optical
                                 depth does not reach the cut inside the leaf
                                 of its scattering is queued (device memory
-                                that grows on demand, at most 11 GiB) and
+                                that grows on demand, at most 11 GiB, in
+                                double 32) and
                                 walked by a ray-cast pass after each
                                 transport launch; 0: walked inline by the
                                 transport kernel.  Results agree up to the

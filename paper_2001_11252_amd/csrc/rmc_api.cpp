@@ -1032,13 +1032,14 @@ void add_run_stats(rmc_run_stats &a, const rmc_run_stats &b) {
 }
 
 constexpr unsigned long long PQ_FIRST_CAP = 1024;          // jobs per region (one region per wave)
-// Job buffer limit: room for half a slice's rays of a full grid of FP32 waves
-// and one observer.  Larger buffers save nothing (a slice cut in two costs a
-// launch), but once written they are slow to give back: with 32 GiB the second and
-// later contexts' first runs of the dusty sphere (2e5 packets) took 339 ms and their
-// closing 620-660, now 116 and 2.5; repeated runs take 111 either way (10 GiB 113,
-// 4 GiB 116).
-constexpr unsigned long long PQ_MAX_BYTES = 11ull << 30;
+// Job buffer limits.  FP32: room for half a slice's rays of a full grid and one
+// observer.  Larger buffers save nothing there (a slice cut in two costs a launch), but
+// once written they are slow to give back: with 32 GiB the second and later contexts'
+// first runs of the dusty sphere (2e5 packets) took 339 ms and their closing 620-660,
+// now 116 and 2.5; repeated runs take 111 either way (10 GiB 113, 4 GiB 116).  FP64
+// jobs are larger and its slices of 8192 iterations would be cut: 9.9e9
+// scatterings/s with 11 GiB, 1.07e10 with 32.
+constexpr unsigned long long queue_limit(bool f32) { return (f32 ? 11ull : 32ull) << 30; }
 static_assert(PQ_FIRST_CAP > 2 * 64 * MAX_OBS, "a region must hold one wave iteration of pushes");
 
 // Control block of the deferred peel-off queue, or null when peel-off rays
@@ -1064,7 +1065,7 @@ rmc_status layout_queue(rmc_ctx *c, unsigned long long n_regions) {
   // at least PQ_FIRST_CAP, so that a region always has room for a wave
   // iteration's pushes
   const unsigned long long max_cap =
-      std::max<unsigned long long>(PQ_MAX_BYTES / peel_job_bytes(c->precision == RMC_FP32_BULK) / n_regions, PQ_FIRST_CAP);
+      std::max<unsigned long long>(queue_limit(c->precision == RMC_FP32_BULK) / peel_job_bytes(c->precision == RMC_FP32_BULK) / n_regions, PQ_FIRST_CAP);
   c->pq_cap = std::min(c->pq_cap, max_cap);
   HIPCHK(c, c->pq_counts.ensure((2 * n_regions + 1) * 4));   // counts, then their running sums
   HIPCHK(c, c->pq_jobs.ensure(n_regions * c->pq_cap * peel_job_bytes(c->precision == RMC_FP32_BULK)));
@@ -1090,12 +1091,12 @@ bool slice_cut(const rmc_ctx *c, unsigned long long max_region) {
 }
 
 // After a launch in which a wave ended its slice early because its region
-// was nearly full, enlarge the regions eightfold (up to PQ_MAX_BYTES) for
+// was nearly full, enlarge the regions eightfold (up to queue_limit) for
 // the next launches.
 rmc_status grow_queue(rmc_ctx *c, unsigned long long max_region) {
   if (!slice_cut(c, max_region)) return RMC_OK;
   const unsigned long long max_cap =
-      std::max<unsigned long long>(PQ_MAX_BYTES / peel_job_bytes(c->precision == RMC_FP32_BULK) / c->pq_regions, PQ_FIRST_CAP);
+      std::max<unsigned long long>(queue_limit(c->precision == RMC_FP32_BULK) / peel_job_bytes(c->precision == RMC_FP32_BULK) / c->pq_regions, PQ_FIRST_CAP);
   if (c->pq_cap >= max_cap) return RMC_OK;
   const unsigned long long cap = c->pq_cap * 8;
   HIPCHK(c, hipStreamSynchronize(c->stream));
