@@ -56,6 +56,9 @@ enum { RMC_F32 = 0, RMC_F64 = 1 };                 /* element type of outputs  *
 enum { RMC_DOM_BOX = 0, RMC_DOM_SLAB_Z = 1, RMC_DOM_SPHERE = 2 };
 enum { RMC_PHASE_LYA_DIPOLE = 0, RMC_PHASE_ISOTROPIC = 1 };
 enum { RMC_ST_NONE = 0, RMC_ST_ESCAPED = 1, RMC_ST_ABSORBED = 2, RMC_ST_STUCK = 3 };
+/* Options of rmc_set_option.  A run, a batch or a stream takes them as they
+   are when it begins: one set while a stream is open (rmc_stream_begin,
+   rmc_batch_begin) is accepted and holds from the next begin on. */
 enum {
   RMC_OPT_FORWARD_ONLY = 1,  /* 1: scatterings keep direction and frequency
                                 (the precision test of Sect. 4.5)            */

@@ -150,6 +150,11 @@ struct rmc_ctx {
   int s_walk_lp = 0;         // log2 of the packets of each of them
   int64_t s_total = 0, s_started = 0, s_done = 0;
   int s_grid = 0, s_levels = 1, s_nprobs = 0;
+  // the options that shape the stream's launches and buffers, as they were at
+  // its begin: slots, reserves and queue regions are sized for them, and a packet
+  // parked with a pending event needs the kernel that left it so
+  int s_block = 64, s_refill = 1, s_slice_iters = 1;
+  bool s_regroup = false, s_compact = false;
   bool s_open = false, s_batch = false;
   const ProblemK *s_probs = nullptr;
   const int64_t *s_starts = nullptr;
@@ -1143,9 +1148,14 @@ rmc_status stream_open(rmc_ctx *c, int64_t total, int n_probs, int levels, bool 
   c->s_nprobs = n_probs;
   c->s_levels = std::max(levels, 1);
   c->s_batch = batch;
+  c->s_block = c->block;
+  c->s_refill = c->refill;
+  c->s_slice_iters = c->slice_iters;
+  c->s_regroup = c->regroup != 0;
+  c->s_compact = c->compact != 0;
   c->s_grid = grid_for(c, total, batch, levels);
   c->s_tail_grid = c->s_walk_waves = 0;
-  const int64_t n_slots = (int64_t)c->s_grid * c->block;
+  const int64_t n_slots = (int64_t)c->s_grid * c->s_block;
   HIPCHK(c, c->slots.ensure((size_t)n_slots * slot_bytes()));
   HIPCHK(c, c->d_slice.ensure((N_STATS + 4) * 8));
   const int n_waves = (int)(n_slots / 64);
@@ -1156,7 +1166,7 @@ rmc_status stream_open(rmc_ctx *c, int64_t total, int n_probs, int levels, bool 
     // a region per wave of the full grid, or of the walkers' launches later on
     // (of both where they share the first launch)
     int lp = 0;
-    const int64_t walkers = c->compact ? std::min<int64_t>((int64_t)c->num_cus * 4, 2 * total) : 0;
+    const int64_t walkers = c->s_compact ? std::min<int64_t>((int64_t)c->num_cus * 4, 2 * total) : 0;
     const bool both = walker_waves(c, total, n_probs, &lp) > 0;
     rmc_status r = layout_queue(c, (unsigned long long)(both ? n_waves + walkers : std::max<int64_t>(n_waves, walkers)));
     if (r) return r;
@@ -1173,15 +1183,15 @@ rmc_status stream_open(rmc_ctx *c, int64_t total, int n_probs, int levels, bool 
 rmc_status stream_graphs(rmc_ctx *c) {
   const int n_probs = c->s_nprobs;
   const bool batch = c->s_batch;
-  const int64_t n_slots = (int64_t)c->s_grid * c->block;
+  const int64_t n_slots = (int64_t)c->s_grid * c->s_block;
   // one slice = zero the slice counters, one transport launch; captured
   // once per shape and replayed
   char key[256];
   PeelQueue *pq = c->s_pq;
   snprintf(key, sizeof key, "%p/%p/%p/%p/%p/%p/%d/%d/%d/%d/%d/%d/%d/%d/%d", (void *)c->s_probs, (void *)c->s_starts,
-           c->slots.p, c->d_slice.p, c->d_next.p, (void *)pq, n_probs, c->s_grid, c->block, c->refill, c->s_levels,
-           c->precision, c->slice_iters, (int)batch,
-           (int)c->s_one * 32 + (int)c->regroup * 16 + c->s_nl * 2 + (int)c->s_defer);
+           c->slots.p, c->d_slice.p, c->d_next.p, (void *)pq, n_probs, c->s_grid, c->s_block, c->s_refill, c->s_levels,
+           c->precision, c->s_slice_iters, (int)batch,
+           (int)c->s_one * 32 + (int)c->s_regroup * 16 + c->s_nl * 2 + (int)c->s_defer);
   if (c->s_key != key || !c->s_graph) {
     for (hipGraphExec_t *ge : {&c->s_graph, &c->s_graph2})
       if (*ge) {
@@ -1198,10 +1208,10 @@ rmc_status stream_graphs(rmc_ctx *c) {
       if (part == 0) {
         if (e == hipSuccess) e = launch_fill_u64(c->d_slice.as<unsigned long long>(), N_STATS + 4, 0ull, cap);
         if (e == hipSuccess)
-          e = launch_transport(f32, batch, c->s_defer, c->s_nl, c->regroup != 0, c->s_probs, c->s_starts,
+          e = launch_transport(f32, batch, c->s_defer, c->s_nl, c->s_regroup, c->s_probs, c->s_starts,
                                n_probs,
-                               c->d_next.as<unsigned long long>(), c->refill, c->s_levels, c->s_grid, c->block,
-                               c->slots.p, c->slice_iters, c->d_slice.as<unsigned long long>(), cap);
+                               c->d_next.as<unsigned long long>(), c->s_refill, c->s_levels, c->s_grid, c->s_block,
+                               c->slots.p, c->s_slice_iters, c->d_slice.as<unsigned long long>(), cap);
       } else {
         const int grid = c->num_cus * peel_drain_blocks_per_cu(f32, batch, c->s_one, c->s_nl, c->s_levels);
         if (e == hipSuccess)
@@ -1228,8 +1238,8 @@ rmc_status stream_graphs(rmc_ctx *c) {
 // front of the other slot array, for the walkers' launches (waves of 2^lp) or,
 // with waves 0, for the transport; *d_live becomes their count.
 rmc_status gather_slots(rmc_ctx *c, int64_t live, int64_t lanes, int waves, int lp) {
-  const int new_grid = (int)((live + c->block - 1) / c->block);
-  const int64_t n_new = waves > 0 ? (int64_t)waves << lp : (int64_t)new_grid * c->block;
+  const int new_grid = (int)((live + c->s_block - 1) / c->s_block);
+  const int64_t n_new = waves > 0 ? (int64_t)waves << lp : (int64_t)new_grid * c->s_block;
   DevBuf &dst = c->s_slots == c->slots2.p ? c->slots : c->slots2;
   HIPCHK(c, dst.ensure((size_t)n_new * slot_bytes()));
   const int64_t n_work = 1 + (c->s_batch ? (c->s_nprobs + 1) / 2 : 0);   // the live count, then 32 bits a problem
@@ -1261,7 +1271,7 @@ rmc_status gather_slots(rmc_ctx *c, int64_t live, int64_t lanes, int waves, int 
 rmc_status gather_tail(rmc_ctx *c) {
   const int64_t live = c->s_total - c->s_done;
   const int64_t lanes = c->s_walk_waves > 0 ? (int64_t)c->s_walk_waves << c->s_walk_lp
-                                            : (int64_t)(c->s_tail_grid > 0 ? c->s_tail_grid : c->s_grid) * c->block;
+                                            : (int64_t)(c->s_tail_grid > 0 ? c->s_tail_grid : c->s_grid) * c->s_block;
   if (live <= 0 || live > lanes * 3 / 4) return RMC_OK;
   int lp = 0;
   const int waves = c->s_defer ? walker_waves(c, live, c->s_nprobs, &lp) : 0;
@@ -1301,19 +1311,21 @@ rmc_status stream_launch(rmc_ctx *c, int budget, bool start_walkers, rmc_run_sta
     HIPCHK(c, hipEventRecord(c->ev0, c->stream));
     HIPCHK(c, launch_fill_u64(d_slice, N_STATS + 4, 0ull, c->stream));
     if (c->s_walk_waves == 0) {
-      HIPCHK(c, launch_transport(f32, c->s_batch, c->s_defer, c->s_nl, c->regroup != 0, c->s_probs, c->s_starts,
-                                 c->s_nprobs, c->d_next.as<unsigned long long>(), c->refill, c->s_levels, tg, c->block,
+      HIPCHK(c, launch_transport(f32, c->s_batch, c->s_defer, c->s_nl, c->s_regroup, c->s_probs, c->s_starts,
+                                 c->s_nprobs, c->d_next.as<unsigned long long>(), c->s_refill, c->s_levels, tg, c->s_block,
                                  c->s_slots, start_walkers ? 1 : budget, d_slice, c->stream));
-      regions = tg * (c->block / 64);
+      regions = tg * (c->s_block / 64);
       if (start_walkers) {
         int lp = 0;
         const int waves = walker_waves(c, c->s_total, c->s_nprobs, &lp);
-        rmc_status r = gather_slots(c, c->s_total, (int64_t)tg * c->block, waves, lp);
+        rmc_status r = gather_slots(c, c->s_total, (int64_t)tg * c->s_block, waves, lp);
         if (r) return r;
         --budget;
       }
     }
     if (c->s_walk_waves > 0) {
+      if (c->s_pq && (unsigned long long)(regions + c->s_walk_waves) > c->pq_regions)
+        return fail(c, RMC_EDEVICE, "peel-off queue: %llu regions, %d needed", c->pq_regions, regions + c->s_walk_waves);
       HIPCHK(c, launch_walkers(f32, c->s_batch, c->s_nl, c->s_probs, regions, c->s_levels, c->s_slots,
                                c->s_walk_lp, c->s_walk_waves, budget, d_slice, c->stream));
       regions += c->s_walk_waves;
@@ -1358,20 +1370,20 @@ rmc_status stream_step(rmc_ctx *c, rmc_run_stats *slice, int64_t *remaining) {
     return RMC_OK;
   }
   int lp;
-  const bool start_walkers = c->s_started == 0 && c->compact && c->s_defer && c->slice_iters > 1 &&
-                             (int64_t)c->s_grid * c->block >= c->s_total &&
+  const bool start_walkers = c->s_started == 0 && c->s_compact && c->s_defer && c->s_slice_iters > 1 &&
+                             (int64_t)c->s_grid * c->s_block >= c->s_total &&
                              walker_waves(c, c->s_total, c->s_nprobs, &lp) > 0;
   // Gathered slots that are too many for the walkers run half a slice: those
   // near their end leave few enough for them (1.5e5 FP64 packets of 2000 events, first
   // run of a context, whose launches the queue's growth shifts: 56 ms with whole
   // slices, 50.5 with halves; an eighth cost the FP32 spheres 2%).
-  const int budget = c->s_tail_grid > 0 ? std::max(c->slice_iters / 2, 1) : c->slice_iters;
+  const int budget = c->s_tail_grid > 0 ? std::max(c->s_slice_iters / 2, 1) : c->s_slice_iters;
   rmc_status r = stream_launch(c, budget, start_walkers, &z);
   if (r) return r;
   add_run_stats(c->s_acc, z);
   if (slice) *slice = z;
   if (remaining) *remaining = c->s_total - c->s_done;
-  if (c->compact && c->s_started >= c->s_total && c->s_done < c->s_total) return gather_tail(c);
+  if (c->s_compact && c->s_started >= c->s_total && c->s_done < c->s_total) return gather_tail(c);
   return RMC_OK;
 }
 
