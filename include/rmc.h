@@ -71,8 +71,9 @@ enum {
   RMC_OPT_PEEL_DEFER = 6,    /* 1 (default): a peel-off ray whose optical
                                 depth does not reach the cut inside the leaf
                                 of its scattering is queued (device memory
-                                that grows on demand, at most 11 GiB, in
-                                double 32) and
+                                that grows on demand, at most 32 GiB; in
+                                float 11 GiB per observer and 2048
+                                iterations of a slice if that is less) and
                                 walked by a ray-cast pass after each
                                 transport launch; 0: walked inline by the
                                 transport kernel.  Results agree up to the

@@ -174,6 +174,7 @@ struct rmc_ctx {
   int tp_obs = -1;
   int64_t tp_n = 0;
   uint64_t tp_gen = 0;
+  unsigned long long s_max_obs = 1;  // most observers of a problem of the stream
   int s_nl = 1;                      // lines the stream's kernels are compiled for (lines_for)
   bool s_one = false;                // its ray-cast pass serves one observer of one problem
   bool s_defer = true;               // transport kernel without the inline peel-off walker
@@ -1037,14 +1038,22 @@ void add_run_stats(rmc_run_stats &a, const rmc_run_stats &b) {
 }
 
 constexpr unsigned long long PQ_FIRST_CAP = 1024;          // jobs per region (one region per wave)
-// Job buffer limits.  FP32: room for half a slice's rays of a full grid and one
-// observer.  Larger buffers save nothing there (a slice cut in two costs a launch), but
-// once written they are slow to give back: with 32 GiB the second and later contexts'
-// first runs of the dusty sphere (2e5 packets) took 339 ms and their closing 620-660,
-// now 116 and 2.5; repeated runs take 111 either way (10 GiB 113, 4 GiB 116).  FP64
-// jobs are larger and its slices of 8192 iterations would be cut: 9.9e9
-// scatterings/s with 11 GiB, 1.07e10 with 32.
-constexpr unsigned long long queue_limit(bool f32) { return (f32 ? 11ull : 32ull) << 30; }
+// Job buffer limit: 32 GiB, in FP32 less where half a slice's rays of a full
+// grid need less (11 GiB for one observer and slices of 2048 iterations).  More
+// than that saves little there (a slice cut in two costs a launch: 4e5 dusty-sphere
+// packets to 8000 events 117.4 ms with 11 GiB, 115.0 with 32), and large buffers,
+// once written, are slow to give back: of contexts that follow each other within
+// half a second some wait 0.2 to 3 s in their closing or in the next one's first
+// run, with 32 GiB most of these packets' contexts, with 11 few.  With more rays
+// a slice 11 GiB would cut every one of them: the same packets toward three
+// observers 393 ms (367 with 32 GiB), one observer in slices of 8192 iterations
+// 147 (121 with 32).  FP64 jobs are larger: 9.9e9 scatterings/s in slices of 8192
+// with 11 GiB, 1.07e10 with 32.
+unsigned long long queue_limit(const rmc_ctx *c) {
+  if (c->precision != RMC_FP32_BULK) return 32ull << 30;
+  const unsigned long long rays = c->s_max_obs * (unsigned long long)std::max(c->s_slice_iters, 2048);
+  return std::min((11ull << 30) / 2048 * rays, 32ull << 30);
+}
 static_assert(PQ_FIRST_CAP > 2 * 64 * MAX_OBS, "a region must hold one wave iteration of pushes");
 
 // Control block of the deferred peel-off queue, or null when peel-off rays
@@ -1069,8 +1078,8 @@ rmc_status peel_queue(rmc_ctx *c, PeelQueue **out) {
 rmc_status layout_queue(rmc_ctx *c, unsigned long long n_regions) {
   // at least PQ_FIRST_CAP, so that a region always has room for a wave
   // iteration's pushes
-  const unsigned long long max_cap =
-      std::max<unsigned long long>(queue_limit(c->precision == RMC_FP32_BULK) / peel_job_bytes(c->precision == RMC_FP32_BULK) / n_regions, PQ_FIRST_CAP);
+  const unsigned long long max_cap = std::max<unsigned long long>(
+      queue_limit(c) / peel_job_bytes(c->precision == RMC_FP32_BULK) / n_regions, PQ_FIRST_CAP);
   c->pq_cap = std::min(c->pq_cap, max_cap);
   HIPCHK(c, c->pq_counts.ensure((2 * n_regions + 1) * 4));   // counts, then their running sums
   HIPCHK(c, c->pq_jobs.ensure(n_regions * c->pq_cap * peel_job_bytes(c->precision == RMC_FP32_BULK)));
@@ -1100,8 +1109,8 @@ bool slice_cut(const rmc_ctx *c, unsigned long long max_region) {
 // the next launches.
 rmc_status grow_queue(rmc_ctx *c, unsigned long long max_region) {
   if (!slice_cut(c, max_region)) return RMC_OK;
-  const unsigned long long max_cap =
-      std::max<unsigned long long>(queue_limit(c->precision == RMC_FP32_BULK) / peel_job_bytes(c->precision == RMC_FP32_BULK) / c->pq_regions, PQ_FIRST_CAP);
+  const unsigned long long max_cap = std::max<unsigned long long>(
+      queue_limit(c) / peel_job_bytes(c->precision == RMC_FP32_BULK) / c->pq_regions, PQ_FIRST_CAP);
   if (c->pq_cap >= max_cap) return RMC_OK;
   const unsigned long long cap = c->pq_cap * 8;
   HIPCHK(c, hipStreamSynchronize(c->stream));
@@ -1405,6 +1414,7 @@ rmc_status stream_begin_single(rmc_ctx *c, uint64_t seed, int64_t first, int64_t
   c->pb_host.index = 0;
   c->s_nl = lines_for(c);
   c->s_one = c->obs.size() == 1;
+  c->s_max_obs = c->obs.size();
   c->starts_host[0] = 0;
   c->starts_host[1] = n;
   HIPCHK(c, c->d_prob.ensure(sizeof(ProblemK)));
@@ -1894,7 +1904,11 @@ rmc_status batch_open(rmc_ctx *const *P, int np, const uint64_t *seeds, const in
   c0->s_defer = c0->s_pq != nullptr || !any_obs;
   c0->s_nl = 1;
   c0->s_one = false;
-  for (int i = 0; i < np; ++i) c0->s_nl = std::max(c0->s_nl, lines_for(P[i]));
+  c0->s_max_obs = 1;
+  for (int i = 0; i < np; ++i) {
+    c0->s_nl = std::max(c0->s_nl, lines_for(P[i]));
+    c0->s_max_obs = std::max<unsigned long long>(c0->s_max_obs, P[i]->obs.size());
+  }
   c0->b_host.resize(np);
   c0->b_starts_host.assign(np + 1, 0);
   for (int i = 0; i < np; ++i) {
