@@ -1647,11 +1647,13 @@ template <class R, bool PRODUCT> struct RayWalk {
   int X[3];
   Cell c;
   LeafRec<R> lf;
+  bool by_quotient;
 
   // The leaf of p; false outside the unit cube.
   template <class PB>
   __device__ __forceinline__ bool start(const PB &pb, const double k[3], int *stk, int stride) {
     if (!int_coords(pb.L, p, k, X)) return false;
+    by_quotient = quotient_holds(p, k);
     locate(pb, X, stk, stride, c);
     lf = load_leaf<R>(pb.leaves, c.leaf);
     return true;
@@ -1673,7 +1675,7 @@ template <class R, bool PRODUCT> struct RayWalk {
         lo[d] = (double)o[d] * inv;
         hi[d] = (double)(o[d] + sz) * inv;
         const double a = (k[d] > 0.0 ? hi[d] : lo[d]) - p[d];
-        t[d] = PRODUCT ? a * kinv[d] : (fabs(k[d]) >= QUOTIENT_MIN ? quotient(a, k[d], kinv[d]) : a / k[d]);
+        t[d] = PRODUCT ? a * kinv[d] : (by_quotient ? quotient(a, k[d], kinv[d]) : a / k[d]);
         te = t[d] < te ? t[d] : te;
       }
     }
@@ -1987,7 +1989,7 @@ __global__ void __launch_bounds__(256) k_tau(ProblemK pb, int64_t n, const doubl
   const double k[3] = {dir[3 * r], dir[3 * r + 1], dir[3 * r + 2]};
   double kinv[3];
 #pragma unroll
-  for (int d = 0; d < 3; ++d) kinv[d] = fabs(k[d]) >= QUOTIENT_MIN ? 1.0 / k[d] : 0.0;
+  for (int d = 0; d < 3; ++d) kinv[d] = 1.0 / k[d];
   uint32_t nc = 0;
   tau_out[r] = walk_tau<R, NL, false>(pb, p, k, kinv, x_ext[r], __builtin_inf(), stk, blockDim.x, &nc);
 }

@@ -164,15 +164,30 @@ __host__ __device__ inline double atan_any(double z) {
 // a / b rounded to nearest, from y = 1 / b rounded to nearest (computed once
 // per ray): a y is within two ulp, the first correction brings it within one,
 // and from there a correction by the exact fma remainder rounds correctly
-// (Markstein 1990).  Five instructions against the dozen of a division.  b not
-// below 2^-1000 in magnitude (reciprocal) and a no smaller than the path's
-// differences of coordinates (2^-60 or 0), so nothing under- or overflows.
+// (Markstein 1990).  Five instructions against the dozen of a division.  The
+// remainder is exact and nothing under- or overflows for |a| between 2^-900 and
+// 2^20 (or 0) and |b| between 2^-1000 and 2^60 (quotient_holds).
 __host__ __device__ inline double quotient(double a, double b, double y) {
   double q = a * y;
   q = fma(fma(-b, q, a), y, q);
   return fma(fma(-b, q, a), y, q);
 }
-constexpr double QUOTIENT_MIN = 0x1p-1000;
+
+// Whether quotient() divides the distances of a ray from p along k to the faces
+// of its cells: a caller's start may lie closer to a face at 0 than any normal
+// number, and its direction may have any length.  A face's distance is at least
+// 2^-70, or the coordinate itself where the face is at 0; moving on, a coordinate
+// becomes 0 or keeps 2^-106 of its size where it cancels against the step to all
+// bits, which takes eight times in a row to leave quotient's range.
+__host__ __device__ inline bool quotient_holds(const double p[3], const double k[3]) {
+  bool ok = true;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const double b = fabs(k[d]);
+    ok = ok && (b == 0.0 || (b >= 0x1p-1000 && b <= 0x1p60)) && (p[d] == 0.0 || p[d] >= 0x1p-50);
+  }
+  return ok;
+}
 
 #pragma clang fp contract(fast)
 
