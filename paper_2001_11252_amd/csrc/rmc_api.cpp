@@ -149,6 +149,7 @@ struct rmc_ctx {
   int s_walk_waves = 0;      // >0: waves of the walkers' launches (gathered slots)
   int s_walk_lp = 0;         // log2 of the packets of each of them
   int64_t s_total = 0, s_started = 0, s_done = 0;
+  int64_t s_iters = 0;       // loop iterations per lane of the last step's launch
   int s_grid = 0, s_levels = 1, s_nprobs = 0;
   // the options that shape the stream's launches and buffers, as they were at
   // its begin: slots, reserves and queue regions are sized for them, and a packet
@@ -1166,7 +1167,7 @@ rmc_status stream_open(rmc_ctx *c, int64_t total, int n_probs, int levels, bool 
   c->s_tail_grid = c->s_walk_waves = 0;
   const int64_t n_slots = (int64_t)c->s_grid * c->s_block;
   HIPCHK(c, c->slots.ensure((size_t)n_slots * slot_bytes()));
-  HIPCHK(c, c->d_slice.ensure((N_STATS + 4) * 8));
+  HIPCHK(c, c->d_slice.ensure((N_STATS + 5) * 8));
   const int n_waves = (int)(n_slots / 64);
   HIPCHK(c, c->d_next.ensure((RESERVE_OFFSET + 2 * (size_t)n_waves) * 8));
   c->s_slots = c->slots.p;
@@ -1215,7 +1216,7 @@ rmc_status stream_graphs(rmc_ctx *c) {
       hipGraph_t g = nullptr;
       e = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
       if (part == 0) {
-        if (e == hipSuccess) e = launch_fill_u64(c->d_slice.as<unsigned long long>(), N_STATS + 4, 0ull, cap);
+        if (e == hipSuccess) e = launch_fill_u64(c->d_slice.as<unsigned long long>(), N_STATS + 5, 0ull, cap);
         if (e == hipSuccess)
           e = launch_transport(f32, batch, c->s_defer, c->s_nl, c->s_regroup, c->s_probs, c->s_starts,
                                n_probs,
@@ -1305,6 +1306,7 @@ rmc_status gather_tail(rmc_ctx *c) {
 // host in between (their waves are those that all packets would need).
 rmc_status stream_launch(rmc_ctx *c, int budget, bool start_walkers, rmc_run_stats *z) {
   const bool f32 = c->precision == RMC_FP32_BULK;
+  const int asked = budget;
   unsigned long long *d_slice = c->d_slice.as<unsigned long long>();
   int regions = 0;   // of the peel-off queue that the launch fills
   if (c->s_walk_waves == 0 && c->s_tail_grid == 0 && !start_walkers) {
@@ -1318,7 +1320,7 @@ rmc_status stream_launch(rmc_ctx *c, int budget, bool start_walkers, rmc_run_sta
     // the captured launches with the shape of the gathered slots
     const int tg = c->s_tail_grid > 0 ? c->s_tail_grid : c->s_grid;
     HIPCHK(c, hipEventRecord(c->ev0, c->stream));
-    HIPCHK(c, launch_fill_u64(d_slice, N_STATS + 4, 0ull, c->stream));
+    HIPCHK(c, launch_fill_u64(d_slice, N_STATS + 5, 0ull, c->stream));
     if (c->s_walk_waves == 0) {
       HIPCHK(c, launch_transport(f32, c->s_batch, c->s_defer, c->s_nl, c->s_regroup, c->s_probs, c->s_starts,
                                  c->s_nprobs, c->d_next.as<unsigned long long>(), c->s_refill, c->s_levels, tg, c->s_block,
@@ -1346,7 +1348,7 @@ rmc_status stream_launch(rmc_ctx *c, int budget, bool start_walkers, rmc_run_sta
                                   d_slice, c->stream));
   }
   HIPCHK(c, hipEventRecord(c->ev2, c->stream));
-  unsigned long long h[N_STATS + 4];
+  unsigned long long h[N_STATS + 5];
   HIPCHK(c, hipMemcpyAsync(h, d_slice, sizeof h, hipMemcpyDeviceToHost, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   float ms = 0.f, ms2 = 0.f;
@@ -1366,6 +1368,7 @@ rmc_status stream_launch(rmc_ctx *c, int budget, bool start_walkers, rmc_run_sta
   }
   c->s_done += (int64_t)h[S_EMITTED];
   c->s_started += (int64_t)h[N_STATS + 3];
+  c->s_iters = h[N_STATS + 4] ? (int64_t)h[N_STATS + 4] : asked;
   return RMC_OK;
 }
 
@@ -2037,7 +2040,7 @@ rmc_status autotune_trials(rmc_ctx *const *P, int np, const uint64_t *seeds, con
             work += (double)st.scatterings + (double)st.crossings + (double)st.peel_crossings;
             ms += wall;
           }
-          done += sl;
+          done += c0->s_iters;   // (a launch that finds the queue dry, or runs gathered packets, is shorter)
           if (rem == 0) break;
         }
         c0->s_open = false;

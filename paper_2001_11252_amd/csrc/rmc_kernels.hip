@@ -945,14 +945,16 @@ __global__ void __launch_bounds__(256)
   const int wib = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int64_t wave = (int64_t)blockIdx.x * (stride >> 6) + wib;
   PeelSink<R> snk;
-  // per wave: queued rays, then the packets that escaped, were absorbed, got stuck
-  int *const wcnt = lds + 2 * stack_levels * stride + 4 * wib;
+  // per wave: queued rays, then the packets that escaped, were absorbed, got stuck,
+  // then the passes run when the queue was last found dry (kept here: a value that
+  // left the loop by each of its exits would cost the float kernels 150 spills)
+  int *const wcnt = lds + 2 * stack_levels * stride + 5 * wib;
   snk.count = wcnt;
   snk.region = queue ? (PeelJob<R> *)pq->jobs + (size_t)wave * pq->cap : nullptr;
   snk.cap = queue ? (uint32_t)pq->cap : 0u;
   snk.lost = queue ? &pq->lost : nullptr;
   const int room = queue ? (int)pq->cap - 2 * 64 * MAX_OBS : 0x7fffffff;
-  if (lane < 4) wcnt[lane] = 0;
+  if (lane < 5) wcnt[lane] = 0;
 
   // the wave's reserve of packets taken from the queue and not started yet
   unsigned long long *const reserve = next + RESERVE_OFFSET + 2 * wave;
@@ -989,7 +991,13 @@ __global__ void __launch_bounds__(256)
   int dry_at = total > (int64_t)gridDim.x * blockDim.x && !queue_dry(next, total) ? 0 : -1;
   for (int it = 0; it < budget; ++it) {
     if (DEFER && *snk.count > room) break;
-    if (it % DRY_CHECK == DRY_CHECK - 1 && dry_at >= 0 && queue_dry(next, total) && ++dry_at > 1) break;
+    if (it % DRY_CHECK == DRY_CHECK - 1 && dry_at >= 0) {
+      if (queue_dry(next, total)) {
+        wcnt[4] = it + 1;
+        ++dry_at;
+      }
+      if (dry_at > 1) break;
+    }
     // ---- record ended packets and refill idle lanes, together, once the
     // lanes have idled about as much as that costs the wave (REFILL_DEBT
     // lane passes), or none is active
@@ -1151,6 +1159,8 @@ __global__ void __launch_bounds__(256)
     reserve[0] = r_next;
     reserve[1] = r_end;
     if (started) atomicAdd(slice + N_STATS + 3, (unsigned long long)started);
+    // the length of a launch that ends on a dry queue
+    if (wcnt[4]) atomicMax(slice + N_STATS + 4, (unsigned long long)wcnt[4]);
   }
   publish(BATCH ? nullptr : probs[0].stats, acc, wcnt + 1, slice);
 }
@@ -2515,7 +2525,7 @@ static TransportFn transport_fn(bool fp32, bool batch, bool defer, int nl, bool 
 }
 
 static size_t transport_lds(int stack_levels, int block) {
-  return ((size_t)2 * stack_levels * block + 4 * (block / 64)) * sizeof(int);
+  return ((size_t)2 * stack_levels * block + 5 * (block / 64)) * sizeof(int);
 }
 
 hipError_t launch_transport(bool fp32, bool batch, bool defer, int nl, bool regroup, const ProblemK *d_probs,
