@@ -251,7 +251,7 @@ def bench_batch(a, rmc, W):
                  a.steps, a.warmup, 1e3 * wall / a.steps, "f32",
                  {"workload": "batch_64_problems_slab_sphere_lya_mgii", "problems": len(probs),
                   "packets": int(sum(npk)), "tuned": best, "parallelism": "none"},
-                 transport_roofline(tot, kms, "fp32", "k_transport<float,true,true,4>"),
+                 transport_roofline(tot, kms, "fp32", "k_transport<float,true,true,2>"),
                  crossings_per_s=(tot["crossings"] + tot["peel_crossings"]) / wall, cpu_baseline=cpu)
 
 
@@ -442,14 +442,14 @@ def bench_multi_species(a, rmc, W):
                  "packets/s", a.steps, 1, 1e3 * wall / a.steps, "f32",
                  {"workload": "feii_wind_2587_2600_fluorescent_flat_continuum_64cubed", "packets": n,
                   "parallelism": "none"},
-                 transport_roofline(td, kd, "fp32", "k_transport<float,false,true,4>"),
+                 transport_roofline(td, kd, "fp32", "k_transport<float,false,true,2>"),
                  feii_wind={"packets_per_s": n * a.steps / wall, "scatterings_per_s": tot["scatterings"] / wall,
                             "scatterings_per_packet": tot["scatterings"] / (n * a.steps)},
                  deuterium_sphere={"scatterings_per_s": td["scatterings"] / wd,
                                    "transport_ms_avg": sum(kd) / len(kd),
                                    "workload": "static_sphere_NHI2e19_DH3e-5_T1e4_lya_dlya",
                                    "note": "the roofline object is this sphere's transport kernel (two lines: "
-                                           "the multi-line kernel)"},
+                                           "the two-line kernel)"},
                  cpu_baseline=cpu)
 
 

@@ -67,7 +67,9 @@ enum {
   RMC_OPT_BLOCK = 3,         /* threads per block of the transport kernel    */
   RMC_OPT_WAVES_PER_CU = 4,  /* resident waves per CU the grid is sized for  */
   RMC_OPT_REFILL = 5,        /* idle lanes a wave gathers before it takes new
-                                packets (1..64)                              */
+                                packets (1..64); it also waits until its idle
+                                lanes have missed 64 passes of the loop in
+                                all, or every lane is idle                   */
   RMC_OPT_PEEL_DEFER = 6,    /* 1 (default): a peel-off ray whose optical
                                 depth does not reach the cut inside the leaf
                                 of its scattering is queued (device memory
@@ -79,7 +81,13 @@ enum {
                                 transport kernel.  Results agree up to the
                                 order of the cube additions.                 */
   RMC_OPT_SLICE_ITERS = 7,   /* loop iterations (events or cell crossings)
-                                per lane in one transport launch            */
+                                per lane in one transport launch, at most: a
+                                launch of more packets than lanes ends at
+                                most 512 iterations after it has started the
+                                last of them, a wave whose part of the
+                                peel-off queue is full ends early, and
+                                gathered packets (RMC_OPT_COMPACT) run half
+                                of it until they are few                     */
   RMC_OPT_REGROUP = 9,       /* 1: the transport loop runs one rejection
                                 round of a line scattering's atom-velocity
                                 draw per pass; a rejected round leaves the
@@ -284,8 +292,8 @@ rmc_status rmc_reset_cubes(rmc_ctx *ctx);
 rmc_status rmc_run(rmc_ctx *ctx, uint64_t seed, int64_t first, int64_t n,
                    rmc_run_stats *stats);
 /* Streaming form of rmc_run.  begin queues packets [first, first+n) and
- * parks nothing; each step is one bounded launch (RMC_OPT_SLICE_ITERS loop
- * iterations per lane) in which every lane advances the packet it holds,
+ * parks nothing; each step is one bounded launch (at most
+ * RMC_OPT_SLICE_ITERS loop iterations per lane) in which every lane advances the packet it holds,
  * parks it in device memory if it is still alive, and idle lanes take new
  * packets from the queue.  step reports the work of that launch (emitted =
  * packets finished in it = escaped + absorbed + stuck in it; peel_dropped
@@ -394,7 +402,7 @@ rmc_status rmc_batch_begin(rmc_ctx *const *problems, int n_problems, const uint6
 
 /* Pick the transport launch shape for a batch by measurement: every
  * candidate (threads per block x idle lanes a wave gathers before refilling
- * x loop iterations per launch) runs the same stretch of this batch: 8192
+ * x most loop iterations per launch) runs the same stretch of this batch: 8192
  * loop iterations per lane untimed, then `trial_slices` windows of 8192
  * timed (their results are discarded; each launch timed whole,
  * synchronisation included), and the one with the most scatterings plus

@@ -1129,12 +1129,12 @@ rmc_status grow_queue(rmc_ctx *c, unsigned long long max_region) {
 // problems, for each problem to have waves of its own).  Up to eight packets a
 // wave, one wave per CU is faster than fewer packets on more waves, which
 // share the CUs' instruction caches: cycles per event (float slab / float
-// sphere with peel-off) at 1024 packets 4180 / 4444 on 256 waves against
-// 4834 / 4854 on 512 and 6564 / 5839 on 1024; at 4096 packets (16 a wave on
-// 256) 5287 / 5920 against 5628 / 4803 on 1024, and beyond that the more waves
-// the faster.  k_transport took 7118 / 9122 at 1024 packets.
-// FP32 stops at 32 a wave: with 64 a step of 65536 packets with peel-off takes 12440
-// cycles, k_transport 10800 (FP64 22700 against 25600).
+// sphere with peel-off) at 1024 packets 4000 / 4220 on 256 waves against
+// 4900 / 4770 on 512 and 6040 / 5180 on 1024; at 4096 packets (16 a wave on
+// 256) 5130 / 5990 against 5140 / 4440 on 1024, and beyond that the more waves
+// the faster.  k_transport takes 7100 / 9320 at 1024 packets.
+// FP32 stops at 32 a wave: with 64 an event of 65536 packets with peel-off takes
+// 12240 cycles, in k_transport 9870 (FP64 22700 against 25800).
 int walker_waves(const rmc_ctx *c, int64_t live, int n_probs, int *lp) {
   const int64_t extra = std::min<int64_t>(n_probs - 1, live);   // each problem's last wave may be partly filled
   for (const int64_t most : {(int64_t)c->num_cus, (int64_t)c->num_cus * 4}) {

@@ -981,7 +981,8 @@ __device__ __forceinline__ double domain_dist_leaf(const LeafRec<R> &lf, int kin
 }
 
 // Opacity (times box size) of a leaf for a packet at x_ext along k; NL
-// bounds the number of lines (1 for single-line problems, MAX_LINES else).
+// bounds the number of lines: 1, 2 or MAX_LINES in the transport and the
+// ray-cast pass (lines_for), 1 or MAX_LINES in the ray kernels.
 template <class R, int NL = MAX_LINES> struct Opac {
   R kd, kl[NL], x[NL], ktot, w;
 };

@@ -864,15 +864,6 @@ __device__ __forceinline__ unsigned long long uniform64(unsigned long long v) {
   return (unsigned long long)hi << 32 | lo;
 }
 
-// Waves per SIMD the transport kernel is compiled for (register budget,
-// chosen by measurement): the float single-problem kernels with deferred
-// peel-off run four (about 30 registers spill with one line, 40 with four,
-// and they are 8-9% faster than at three), the other float kernels three
-// (no spills; at four the batch kernels spill 50-90 registers and the batch
-// runs slower), the single-problem double kernels with deferred peel-off
-// two (40-55 registers spill, and the dusty sphere runs 38% faster than at
-// one, where nothing spills), the other double kernels (batch, inline
-// walker; 90-200 registers would spill at two) one.
 // Idle lane passes a wave gathers before it records its ended packets and
 // takes new ones.  A refill (emission, point location, the ended packets'
 // outputs) costs the wave about as many instructions as one loop pass does
@@ -885,6 +876,15 @@ __device__ __forceinline__ unsigned long long uniform64(unsigned long long v) {
 #endif
 constexpr uint32_t REFILL_DEBT = RMC_REFILL_DEBT;
 
+// Waves per SIMD the transport kernel is compiled for (register budget,
+// chosen by measurement): the float single-problem kernels with deferred
+// peel-off run four (13 registers spill with one line, 29 with two, 38 with
+// four, and they are 8-9% faster than at three), the other float kernels three
+// (no spills with deferred peel-off; at four the batch kernels spill 50-90
+// registers and the batch runs slower), the single-problem double kernels with
+// deferred peel-off two (39-54 registers spill, and the dusty sphere runs 38%
+// faster than at one, where nothing spills), the other double kernels (batch,
+// inline walker; 90-200 registers would spill at two) one.
 #ifndef RMC_WAVES_F32_LEAN
 #define RMC_WAVES_F32_LEAN 4
 #endif
@@ -1180,9 +1180,9 @@ __global__ void __launch_bounds__(256)
 //     event's peel-off needs in LDS;
 //   - every lane runs the peel-off of one recorded event.
 // The same expressions in the same order per packet as k_transport, so the
-// same packets.  Cycles per event of 64 packets against k_transport built for
-// one wave per SIMD: float 3570 against 6170 (slab, no observer) and 3710
-// against 7940 (one observer), double 6650 / 13420 and 6990 / 17870.
+// same packets.  Cycles per event of 64 packets against k_transport
+// (RMC_OPT_COMPACT 0): float 3480 against 6720 (slab, no observer) and 3620
+// against 9000 (one observer), double 6540 / 16390 and 6840 / 21050.
 
 // Columns of an event's draws in LDS ([column][64]).
 enum {
@@ -2642,11 +2642,14 @@ hipError_t launch_trace(const ProblemK &pb, int64_t n, const double *orig, const
 }
 
 // Threads per block of the ray kernels: one wave where blocks of four waves would
-// not give each of the 256 CUs one.  A ray is a serial chain, and single waves
+// not give each CU one.  A ray is a serial chain, and single waves
 // spread over the CUs.  FP64 optical depths with their copies, blocks of 256 ->
 // of 64 threads: 5000 rays 400 -> 329 us, 20001 rays 436 -> 403; from 65536 rays
 // (525 and 524) to 1e6 both take the same within 2%.
-static int ray_block(int64_t n) { return n < 256 * 256 ? 64 : 256; }
+static int ray_block(int64_t n) {
+  constexpr int64_t cus = 256;   // of the one device this library is compiled for
+  return n < cus * 256 ? 64 : 256;
+}
 
 hipError_t launch_tau(bool fp32, const ProblemK &pb, int64_t n, const double *orig, const double *dir,
                       const double *x, double *tau, hipStream_t st) {

@@ -13,6 +13,9 @@ namespace rmc {
 // fluorescent channels; 2: at most two lines; MAX_LINES).
 // regroup (with defer): one rejection round of a line scattering per pass
 // of the loop, a rejected round leaving the event pending for the next.
+// slice: the launch's N_STATS work counters, then the peel-off jobs queued, the
+// fullest region and the lost pushes (k_peel_scan), the packets started, and the
+// iterations of a launch that ended because the queue ran dry in it (else 0).
 hipError_t launch_transport(bool fp32, bool batch, bool defer, int nl, bool regroup, const ProblemK *d_probs,
                             const int64_t *d_starts, int n_probs, unsigned long long *d_next, int refill_min,
                             int stack_levels, int grid, int block, void *slots, int budget,
