@@ -1643,16 +1643,17 @@ __device__ __forceinline__ uint32_t region_of(const uint32_t *__restrict__ offs,
 // asked for before the current one's opacity is computed: the geometry does not
 // depend on the record, so its load is hidden by that arithmetic (a ray is a
 // chain of dependent reads, and few rays leave nothing else to hide them).
-// Axes the direction does not move along are left out (for an observer along
-// an axis two of three; the tests are the same for every lane then), and the
-// distances are the correctly rounded quotients of exit_dist or, on the float
-// image path, its products with 1/k.
-// Measured, against walks without the early load, dividing and testing all
-// axes, with the lines in a loop: 4e6 FP32 rays of 30 crossings 1148 -> 935 us
-// (image), 1542 -> 1407 (image with crossing lists); 3e5 FP64 rays of 30 crossings
-// 238 -> 221 us (image), 704 -> 594 (adjoint); 20001 FP64 optical depths 458 -> 405 us
-// with their copies.
-template <class R, bool PRODUCT> struct RayWalk {
+// The distances are the correctly rounded quotients of exit_dist or, on the float
+// image path, its products with 1/k.  With AXIS the axes a direction does not move
+// along are branched round; without, all three are computed without a branch, so
+// that their chains overlap: behind branches of their own they ran one after
+// another, and oblique rays were slower than with divisions.
+// Measured in us: walks that divide, without the early load and with the lines in
+// a loop -> branched -> now.  FP64 images along (1,1,1), one line, 6e4 rays 233 ->
+// 227 -> 190, 4e6 rays 3759 -> 4031 -> 3258; two lines, 4e6 rays 2661 -> 3026 ->
+// 2567; FP32, 6e4 rays 187 -> 177 -> 143.  FP64 along z with crossing lists, 3e5 rays
+// 267 -> 235 (AXIS).
+template <class R, bool PRODUCT, bool AXIS> struct RayWalk {
   double p[3];
   int X[3];
   Cell c;
@@ -1678,38 +1679,70 @@ template <class R, bool PRODUCT> struct RayWalk {
     const int side = 1 << pb.L, sz = 1 << (pb.L - c.level);
     const int o[3] = {c.ox, c.oy, c.oz};
     double lo[3], hi[3], t[3], te = __builtin_inf();
+    double pn[3] = {p[0], p[1], p[2]};
+    bool in = true;
+    int Y[3] = {X[0], X[1], X[2]};
+    if constexpr (AXIS) {
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      t[d] = __builtin_inf();
-      if (k[d] != 0.0) {
+      for (int d = 0; d < 3; ++d) {
+        t[d] = __builtin_inf();
+        if (k[d] != 0.0) {
+          lo[d] = (double)o[d] * inv;
+          hi[d] = (double)(o[d] + sz) * inv;
+          const double a = (k[d] > 0.0 ? hi[d] : lo[d]) - p[d];
+          t[d] = PRODUCT ? a * kinv[d] : (by_quotient ? quotient(a, k[d], kinv[d]) : a / k[d]);
+          te = t[d] < te ? t[d] : te;
+        }
+      }
+      te = te < 0.0 ? 0.0 : te;
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        if (k[d] != 0.0) {
+          const double q = fmin(fmax(fma(te, k[d], p[d]), lo[d]), hi[d]);
+          pn[d] = t[d] <= te ? (k[d] > 0.0 ? hi[d] : lo[d]) : q;
+        }
+      }
+      wrap_slab(pb.domain, pn, k);
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        if (k[d] != 0.0) {
+          const double s = pn[d] * sc;
+          const double f = k[d] > 0.0 ? floor(s) : ceil(s) - 1.0;
+          const bool ok = f >= 0.0 && f < (double)side;
+          in = in && ok;
+          Y[d] = ok ? (int)f : 0;
+        }
+      }
+    } else {
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
         lo[d] = (double)o[d] * inv;
         hi[d] = (double)(o[d] + sz) * inv;
-        const double a = (k[d] > 0.0 ? hi[d] : lo[d]) - p[d];
-        t[d] = PRODUCT ? a * kinv[d] : (by_quotient ? quotient(a, k[d], kinv[d]) : a / k[d]);
+        t[d] = (k[d] > 0.0 ? hi[d] : lo[d]) - p[d];
+      }
+      if (PRODUCT) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) t[d] *= kinv[d];
+      } else if (by_quotient) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) t[d] = quotient(t[d], k[d], kinv[d]);
+      } else {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) t[d] /= k[d];
+      }
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        t[d] = k[d] != 0.0 ? t[d] : __builtin_inf();
         te = t[d] < te ? t[d] : te;
       }
-    }
-    te = te < 0.0 ? 0.0 : te;
-    double pn[3] = {p[0], p[1], p[2]};
+      te = te < 0.0 ? 0.0 : te;
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      if (k[d] != 0.0) {
+      for (int d = 0; d < 3; ++d) {
         const double q = fmin(fmax(fma(te, k[d], p[d]), lo[d]), hi[d]);
         pn[d] = t[d] <= te ? (k[d] > 0.0 ? hi[d] : lo[d]) : q;
       }
-    }
-    wrap_slab(pb.domain, pn, k);
-    bool in = true;
-    int Y[3] = {X[0], X[1], X[2]};
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      if (k[d] != 0.0) {
-        const double s = pn[d] * sc;
-        const double f = k[d] > 0.0 ? floor(s) : ceil(s) - 1.0;
-        const bool ok = f >= 0.0 && f < (double)side;
-        in = in && ok;
-        Y[d] = ok ? (int)f : 0;
-      }
+      wrap_slab(pb.domain, pn, k);
+      in = int_coords(pb.L, pn, k, Y);
     }
     *leaf = c.leaf;
     *rec = lf;
@@ -1721,7 +1754,7 @@ template <class R, bool PRODUCT> struct RayWalk {
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
       p[d] = pn[d];
-      X[d] = Y[d];
+      if (AXIS) X[d] = Y[d];
     }
     return true;
   }
@@ -1796,7 +1829,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DrainW
   unsigned long long elem = 0;
   int oi = 0;
   uint32_t steps = 0;
-  RayWalk<R, sizeof(R) == 4> wk;
+  RayWalk<R, sizeof(R) == 4, true> wk;   // (AXIS: 3% faster along z, 3-5% slower along (1,1,1))
   unsigned long long nc_prob = 0, nc_all = 0;
   unsigned long long nd_prob = 0, nd_all = 0;   // float jobs outside the cube
   while (true) {
@@ -1925,12 +1958,12 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DrainW
 // ---------------------------------------------------------- optical depths
 // Optical depth of the ray from p0 along k to the domain border; stops once
 // it reaches tau_cut.
-template <class R, int NL, bool PRODUCT>
+template <class R, int NL, bool PRODUCT, bool AXIS>
 __device__ __forceinline__ double walk_tau(const ProblemK &pb, const double p0[3], const double k[3],
                                            const double kinv[3], double x_ext, double tau_cut, int *stk, int stride,
                                            uint32_t *ncross) {
   const R kr[3] = {(R)k[0], (R)k[1], (R)k[2]};
-  RayWalk<R, PRODUCT> w;
+  RayWalk<R, PRODUCT, AXIS> w;
   w.p[0] = p0[0]; w.p[1] = p0[1]; w.p[2] = p0[2];
   double tau = 0.0;
   bool more = w.start(pb, k, stk, stride);
@@ -2001,12 +2034,14 @@ __global__ void __launch_bounds__(256) k_tau(ProblemK pb, int64_t n, const doubl
 #pragma unroll
   for (int d = 0; d < 3; ++d) kinv[d] = 1.0 / k[d];
   uint32_t nc = 0;
-  tau_out[r] = walk_tau<R, NL, false>(pb, p, k, kinv, x_ext[r], __builtin_inf(), stk, blockDim.x, &nc);
+  tau_out[r] = walk_tau<R, NL, false, false>(pb, p, k, kinv, x_ext[r], __builtin_inf(), stk, blockDim.x, &nc);
 }
 
 // ------------------------------------------------- peel-off image, adjoint
+// Four waves a SIMD also in double, at 4 (one line) and 14 (more) spilled registers:
+// at the three that fit without, 4e6 rays take up to 6% longer.
 template <class R, int NL>
-__global__ void __launch_bounds__(256) k_image_fwd(ProblemK pb, int obs, int64_t n, const double *__restrict__ orig,
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k_image_fwd(ProblemK pb, int obs, int64_t n, const double *__restrict__ orig,
                             const double *__restrict__ x_ext, const double *__restrict__ w,
                             double *__restrict__ image, unsigned long long *__restrict__ ncross) {
   extern __shared__ int lds[];
@@ -2018,7 +2053,7 @@ __global__ void __launch_bounds__(256) k_image_fwd(ProblemK pb, int obs, int64_t
     const double p[3] = {orig[3 * r], orig[3 * r + 1], orig[3 * r + 2]};
     const int pix = pixel_of(ob, p);
     if (pix >= 0) {
-      const double tau = walk_tau<R, NL, sizeof(R) == 4>(pb, p, ob.k, ob.kinv, x_ext[r], TauCut<double>::v, stk,
+      const double tau = walk_tau<R, NL, sizeof(R) == 4, false>(pb, p, ob.k, ob.kinv, x_ext[r], TauCut<double>::v, stk,
                                                          blockDim.x, &nc);
       if (tau < TauCut<double>::v) unsafeAtomicAdd(image + pix, w[r] * exp(-tau));
     }
@@ -2125,7 +2160,7 @@ __device__ __forceinline__ void crossing_grad(const ProblemK &pb, const LeafRec<
 //   dtau/dkappa_d = seg box
 //   dtau/dv_los  = seg nl sum_i kfac_i H'_i dx_i/dw / v_th,ref,
 //   dx_i/dw = -irho inv_mu_i s_i (1 + b x_ext) / (1 + b w)^2.
-template <class R, int NL>
+template <class R, int NL, bool AXIS>
 __global__ void __launch_bounds__(256) k_image_bwd(ProblemK pb, int obs, int64_t n, const double *__restrict__ orig,
                             const double *__restrict__ x_ext, const double *__restrict__ w,
                             const double *__restrict__ G, double inv_vth_ref,
@@ -2140,7 +2175,7 @@ __global__ void __launch_bounds__(256) k_image_bwd(ProblemK pb, int obs, int64_t
   const R kr[3] = {(R)ob.k[0], (R)ob.k[1], (R)ob.k[2]};
   bool walking = false;
   double g = 0.0, xr = 0.0;
-  RayWalk<R, sizeof(R) == 4> wk;
+  RayWalk<R, sizeof(R) == 4, AXIS> wk;
   uint32_t steps = 0;
   if (r < n) {
     const double p0[3] = {orig[3 * r], orig[3 * r + 1], orig[3 * r + 2]};
@@ -2148,7 +2183,7 @@ __global__ void __launch_bounds__(256) k_image_bwd(ProblemK pb, int obs, int64_t
     xr = x_ext[r];
     double tau = TauCut<double>::v;
     if (pix >= 0)
-      tau = walk_tau<R, NL, sizeof(R) == 4>(pb, p0, ob.k, ob.kinv, xr, TauCut<double>::v, stk, blockDim.x, &nc);
+      tau = walk_tau<R, NL, sizeof(R) == 4, AXIS>(pb, p0, ob.k, ob.kinv, xr, TauCut<double>::v, stk, blockDim.x, &nc);
     g = (pix >= 0 && tau < TauCut<double>::v) ? -G[pix] * w[r] * exp(-tau) : 0.0;
     if (g != 0.0) {
       // replay the ray (same traversal as the forward pass)
@@ -2186,7 +2221,7 @@ __global__ void __launch_bounds__(256) k_image_bwd(ProblemK pb, int obs, int64_t
 // requested exceed the capacity and runs the pass again with more).  The
 // walk and the optical depth are those of walk_tau, so the image equals the
 // one k_image_fwd makes, up to the order of the additions.
-template <class R, int NL>
+template <class R, int NL, bool AXIS>
 __global__ void __launch_bounds__(256) k_image_fwd_tape(ProblemK pb, int obs, int64_t n,
                                                         const double *__restrict__ orig,
                                                         const double *__restrict__ x_ext,
@@ -2204,7 +2239,7 @@ __global__ void __launch_bounds__(256) k_image_fwd_tape(ProblemK pb, int obs, in
   bool walking = false;
   int pix = -1;
   double xr = 0.0, tau = 0.0;
-  RayWalk<R, sizeof(R) == 4> wk;
+  RayWalk<R, sizeof(R) == 4, AXIS> wk;
   uint32_t nc = 0;
   if (r < n) {
     wk.p[0] = orig[3 * r]; wk.p[1] = orig[3 * r + 1]; wk.p[2] = orig[3 * r + 2];
@@ -2654,6 +2689,14 @@ static int ray_block(int64_t n) {
   return n < cus * 256 ? 64 : 256;
 }
 
+// Whether an observer's rays move along one axis only: then the double tape and
+// both backward kernels branch round the others (AXIS of RayWalk), 3-5% faster
+// there from 3e5 rays on.  The other ray kernels are no slower without, and rays
+// that move along two axes are faster without in all of them.
+static bool along_axis(const ObsK &ob) {
+  return (ob.k[0] != 0.0) + (ob.k[1] != 0.0) + (ob.k[2] != 0.0) == 1;
+}
+
 hipError_t launch_tau(bool fp32, const ProblemK &pb, int64_t n, const double *orig, const double *dir,
                       const double *x, double *tau, hipStream_t st) {
   const int b = ray_block(n);
@@ -2680,8 +2723,11 @@ hipError_t launch_image_bwd(bool fp32, const ProblemK &pb, int obs, int64_t n, c
                             double *gn, double *gk, double *gv, unsigned long long *ncross, hipStream_t st) {
   const int b = ray_block(n);
   const size_t lds = (size_t)(pb.L > 0 ? pb.L : 1) * b * sizeof(int);
-  const auto fn = fp32 ? (pb.n_lines == 1 ? k_image_bwd<float, 1> : k_image_bwd<float, MAX_LINES>)
-                       : (pb.n_lines == 1 ? k_image_bwd<double, 1> : k_image_bwd<double, MAX_LINES>);
+  const bool axis = along_axis(pb.obs[obs]), one = pb.n_lines == 1;
+  const auto fn = fp32 ? (axis ? (one ? k_image_bwd<float, 1, true> : k_image_bwd<float, MAX_LINES, true>)
+                               : (one ? k_image_bwd<float, 1, false> : k_image_bwd<float, MAX_LINES, false>))
+                       : (axis ? (one ? k_image_bwd<double, 1, true> : k_image_bwd<double, MAX_LINES, true>)
+                               : (one ? k_image_bwd<double, 1, false> : k_image_bwd<double, MAX_LINES, false>));
   hipLaunchKernelGGL(fn, dim3(blocks_for(n, b)), dim3(b), lds, st, pb, obs, n, orig, x, w, G, inv_vth_ref, gn, gk, gv, ncross);
   return hipGetLastError();
 }
@@ -2694,8 +2740,10 @@ hipError_t launch_image_fwd_tape(bool fp32, const ProblemK &pb, int obs, int64_t
   if (n <= 0) return hipSuccess;
   const int b = 256;
   const size_t lds = (size_t)(pb.L > 0 ? pb.L : 1) * b * sizeof(int);
-  const auto fn = fp32 ? (pb.n_lines == 1 ? k_image_fwd_tape<float, 1> : k_image_fwd_tape<float, MAX_LINES>)
-                       : (pb.n_lines == 1 ? k_image_fwd_tape<double, 1> : k_image_fwd_tape<double, MAX_LINES>);
+  const bool axis = along_axis(pb.obs[obs]), one = pb.n_lines == 1;
+  const auto fn = fp32 ? (one ? k_image_fwd_tape<float, 1, false> : k_image_fwd_tape<float, MAX_LINES, false>)
+                       : (axis ? (one ? k_image_fwd_tape<double, 1, true> : k_image_fwd_tape<double, MAX_LINES, true>)
+                               : (one ? k_image_fwd_tape<double, 1, false> : k_image_fwd_tape<double, MAX_LINES, false>));
   hipLaunchKernelGGL(fn, dim3(blocks_for(n, b)), dim3(b), lds, st, pb, obs, n, orig, x, w, image, ncross, tp);
   return hipGetLastError();
 }
