@@ -87,7 +87,8 @@ enum {
                                 last of them, a wave whose part of the
                                 peel-off queue is full ends early, and
                                 gathered packets (RMC_OPT_COMPACT) run half
-                                of it until they are few                     */
+                                of it until they are few (none of this with
+                                RMC_OPT_PEEL_DEFER = 0 and observers)        */
   RMC_OPT_REGROUP = 9,       /* 1: the transport loop runs one rejection
                                 round of a line scattering's atom-velocity
                                 draw per pass; a rejected round leaves the

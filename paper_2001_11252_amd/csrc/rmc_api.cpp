@@ -1388,8 +1388,9 @@ rmc_status stream_step(rmc_ctx *c, rmc_run_stats *slice, int64_t *remaining) {
   // Gathered slots that are too many for the walkers run half a slice: those
   // near their end leave few enough for them (1.5e5 FP64 packets of 2000 events, first
   // run of a context, whose launches the queue's growth shifts: 56 ms with whole
-  // slices, 50.5 with halves; an eighth cost the FP32 spheres 2%).
-  const int budget = c->s_tail_grid > 0 ? std::max(c->s_slice_iters / 2, 1) : c->s_slice_iters;
+  // slices, 50.5 with halves; an eighth cost the FP32 spheres 2%).  With peel-off rays
+  // walked inline no walkers follow.
+  const int budget = c->s_tail_grid > 0 && c->s_defer ? std::max(c->s_slice_iters / 2, 1) : c->s_slice_iters;
   rmc_status r = stream_launch(c, budget, start_walkers, &z);
   if (r) return r;
   add_run_stats(c->s_acc, z);

@@ -987,11 +987,14 @@ __global__ void __launch_bounds__(256)
   // them sooner (1.5e5 FP64 packets of 2000 events on 1.3e5 lanes: the last
   // 19e3 ran 16 ms alone in a launch of full length; the run 50.4 -> 43.8 ms).  A
   // run whose packets all start at once has no such moment, and short walks end
-  // before the second look.
-  int dry_at = total > (int64_t)gridDim.x * blockDim.x && !queue_dry(next, total) ? 0 : -1;
+  // before the second look.  Where peel-off rays are walked inline there are no
+  // walkers, and the packets walk faster spread out than gathered (a wave's step
+  // lasts as long as its longest ray): 3e5 FP32 packets at tau 300, ended early 109
+  // ms, in whole slices 78.
+  int dry_at = DEFER && total > (int64_t)gridDim.x * blockDim.x && !queue_dry(next, total) ? 0 : -1;
   for (int it = 0; it < budget; ++it) {
     if (DEFER && *snk.count > room) break;
-    if (it % DRY_CHECK == DRY_CHECK - 1 && dry_at >= 0) {
+    if (DEFER && it % DRY_CHECK == DRY_CHECK - 1 && dry_at >= 0) {
       if (queue_dry(next, total)) {
         wcnt[4] = it + 1;
         ++dry_at;
@@ -1160,7 +1163,7 @@ __global__ void __launch_bounds__(256)
     reserve[1] = r_end;
     if (started) atomicAdd(slice + N_STATS + 3, (unsigned long long)started);
     // the length of a launch that ends on a dry queue
-    if (wcnt[4]) atomicMax(slice + N_STATS + 4, (unsigned long long)wcnt[4]);
+    if (DEFER && wcnt[4]) atomicMax(slice + N_STATS + 4, (unsigned long long)wcnt[4]);
   }
   publish(BATCH ? nullptr : probs[0].stats, acc, wcnt + 1, slice);
 }
