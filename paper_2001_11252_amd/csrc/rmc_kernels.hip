@@ -876,13 +876,26 @@ __device__ __forceinline__ unsigned long long uniform64(unsigned long long v) {
 #endif
 constexpr uint32_t REFILL_DEBT = RMC_REFILL_DEBT;
 
+// A transport wave's words in LDS: peel-off rays queued, packets that escaped,
+// were absorbed, got stuck; passes run when the queue was last found dry; packets
+// started; whether the queue is long; the wave's reserve [next, end) of it, 64
+// bits each.
+enum { WAVE_QUEUED = 0, WAVE_ENDS = 1, WAVE_DRY = 4, WAVE_STARTED, WAVE_PLENTY, WAVE_NEXT = 8, WAVE_END = 10, WAVE_WORDS = 12 };
+__device__ __forceinline__ void put64(int *p, unsigned long long v) {
+  p[0] = (int)(uint32_t)v;
+  p[1] = (int)(uint32_t)(v >> 32);
+}
+__device__ __forceinline__ unsigned long long get64(const int *p) {
+  return uniform64((unsigned long long)(uint32_t)p[1] << 32 | (uint32_t)p[0]);
+}
+
 // Waves per SIMD the transport kernel is compiled for (register budget,
 // chosen by measurement): the float single-problem kernels with deferred
-// peel-off run four (13 registers spill with one line, 29 with two, 38 with
+// peel-off run four (5 registers spill with one line, 7 with two, 14 with
 // four, and they are 8-9% faster than at three), the other float kernels three
 // (no spills with deferred peel-off; at four the batch kernels spill 50-90
 // registers and the batch runs slower), the single-problem double kernels with
-// deferred peel-off two (39-54 registers spill, and the dusty sphere runs 38%
+// deferred peel-off two (33-44 registers spill, and the dusty sphere runs 38%
 // faster than at one, where nothing spills), the other double kernels (batch,
 // inline walker; 90-200 registers would spill at two) one.
 #ifndef RMC_WAVES_F32_LEAN
@@ -945,22 +958,23 @@ __global__ void __launch_bounds__(256)
   const int wib = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int64_t wave = (int64_t)blockIdx.x * (stride >> 6) + wib;
   PeelSink<R> snk;
-  // per wave: queued rays, then the packets that escaped, were absorbed, got stuck,
-  // then the passes run when the queue was last found dry (kept here: a value that
-  // left the loop by each of its exits would cost the float kernels 150 spills)
-  int *const wcnt = lds + 2 * stack_levels * stride + 5 * wib;
-  snk.count = wcnt;
+  // What the wave needs seldom, in LDS (WAVE_* words; every lane writes the same):
+  // as values of the loop they took scalar registers whose spills cost vector ones
+  // (dusty sphere without observer, launches of 8192 passes: FP64 66.8 -> 65.1 ms,
+  // FP32 41.3 -> 39.5), and a value that left the loop by each of its exits would
+  // cost the float kernels 150 spills.
+  int *const wcnt = lds + 2 * stack_levels * stride + WAVE_WORDS * wib;
+  snk.count = wcnt + WAVE_QUEUED;
   snk.region = queue ? (PeelJob<R> *)pq->jobs + (size_t)wave * pq->cap : nullptr;
   snk.cap = queue ? (uint32_t)pq->cap : 0u;
   snk.lost = queue ? &pq->lost : nullptr;
   const int room = queue ? (int)pq->cap - 2 * 64 * MAX_OBS : 0x7fffffff;
-  if (lane < 5) wcnt[lane] = 0;
+  if (lane < WAVE_WORDS) wcnt[lane] = 0;
 
   // the wave's reserve of packets taken from the queue and not started yet
   unsigned long long *const reserve = next + RESERVE_OFFSET + 2 * wave;
-  unsigned long long r_next = uniform64(reserve[0]), r_end = uniform64(reserve[1]);
-  bool plenty = false;   // enough packets left in the queue for every wave to take more than it needs
-  uint32_t started = 0;
+  put64(wcnt + WAVE_NEXT, uniform64(reserve[0]));
+  put64(wcnt + WAVE_END, uniform64(reserve[1]));
 
   Lane<R> s;
   Lane<R> z;            // counters when this slice took the packet over
@@ -996,7 +1010,7 @@ __global__ void __launch_bounds__(256)
     if (DEFER && *snk.count > room) break;
     if (DEFER && it % DRY_CHECK == DRY_CHECK - 1 && dry_at >= 0) {
       if (queue_dry(next, total)) {
-        wcnt[4] = it + 1;
+        wcnt[WAVE_DRY] = it + 1;
         ++dry_at;
       }
       if (dry_at > 1) break;
@@ -1012,16 +1026,17 @@ __global__ void __launch_bounds__(256)
       debt = 0;
       if (fin != ST_NONE) {
         add_delta(acc, s, z);
-        finish<R, BATCH>(probs[BATCH ? prob : 0], s, fin, wcnt + 1, slice);
+        finish<R, BATCH>(probs[BATCH ? prob : 0], s, fin, wcnt + WAVE_ENDS, slice);
         fin = ST_NONE;
       }
       if (drained) break;
       // packets from the wave's reserve, then from the queue; one atomic
       // takes a wave's worth more than needed while the queue is long
+      unsigned long long r_next = get64(wcnt + WAVE_NEXT), r_end = get64(wcnt + WAVE_END);
       const uint32_t have = (uint32_t)(r_end - r_next);
       unsigned long long base = r_next, lim = r_end;
       if (have < n_idle) {
-        const unsigned long long ask = n_idle - have + (plenty ? 64u : 0u);
+        const unsigned long long ask = n_idle - have + (wcnt[WAVE_PLENTY] ? 64u : 0u);
         if (lane == 0) base = atomicAdd(next, ask);
         base = uniform64(base);
         if (base >= (unsigned long long)total) {
@@ -1029,20 +1044,23 @@ __global__ void __launch_bounds__(256)
           base = lim = (unsigned long long)total;
         } else {
           lim = (unsigned long long)total - base < ask ? (unsigned long long)total : base + ask;
-          plenty = (unsigned long long)total - lim > (unsigned long long)gridDim.x * blockDim.x * 2u;
+          // (enough left for every wave to take more than it needs)
+          wcnt[WAVE_PLENTY] = (unsigned long long)total - lim > (unsigned long long)gridDim.x * blockDim.x * 2u;
         }
       }
       const uint32_t rank = (uint32_t)__popcll(idle & ((1ull << lane) - 1ull));
       const unsigned long long g =
           have >= n_idle || rank < have ? r_next + rank : base + (rank - have);
       const bool take = !active && (rank < have || g < lim);
-      started += (uint32_t)__popcll(__ballot(take));
+      wcnt[WAVE_STARTED] += __popcll(__ballot(take));
       if (have >= n_idle) {
         r_next += n_idle;
       } else {
         r_next = lim - base < n_idle - have ? lim : base + (n_idle - have);
         r_end = lim;
       }
+      put64(wcnt + WAVE_NEXT, r_next);
+      put64(wcnt + WAVE_END, r_end);
       if (take) {
         if (BATCH) {
           int lo = 0, hi = n_probs - 1;
@@ -1145,7 +1163,7 @@ __global__ void __launch_bounds__(256)
   }
   if (fin != ST_NONE) {
     add_delta(acc, s, z);
-    finish<R, BATCH>(probs[BATCH ? prob : 0], s, fin, wcnt + 1, slice);
+    finish<R, BATCH>(probs[BATCH ? prob : 0], s, fin, wcnt + WAVE_ENDS, slice);
   }
   // ---- park the packet (if any) for the next launch, publish the counts
   SlotState &q = slots[gid];
@@ -1159,13 +1177,13 @@ __global__ void __launch_bounds__(256)
     pq->counts[wave] = (uint32_t)*snk.count;
   }
   if (lane == 0) {
-    reserve[0] = r_next;
-    reserve[1] = r_end;
-    if (started) atomicAdd(slice + N_STATS + 3, (unsigned long long)started);
+    reserve[0] = get64(wcnt + WAVE_NEXT);
+    reserve[1] = get64(wcnt + WAVE_END);
+    if (wcnt[WAVE_STARTED]) atomicAdd(slice + N_STATS + 3, (unsigned long long)(uint32_t)wcnt[WAVE_STARTED]);
     // the length of a launch that ends on a dry queue
-    if (DEFER && wcnt[4]) atomicMax(slice + N_STATS + 4, (unsigned long long)wcnt[4]);
+    if (DEFER && wcnt[WAVE_DRY]) atomicMax(slice + N_STATS + 4, (unsigned long long)wcnt[WAVE_DRY]);
   }
-  publish(BATCH ? nullptr : probs[0].stats, acc, wcnt + 1, slice);
+  publish(BATCH ? nullptr : probs[0].stats, acc, wcnt + WAVE_ENDS, slice);
 }
 
 // ------------------------------------------------- the last, longest walks
@@ -2566,7 +2584,7 @@ static TransportFn transport_fn(bool fp32, bool batch, bool defer, int nl, bool 
 }
 
 static size_t transport_lds(int stack_levels, int block) {
-  return ((size_t)2 * stack_levels * block + 5 * (block / 64)) * sizeof(int);
+  return ((size_t)2 * stack_levels * block + WAVE_WORDS * (block / 64)) * sizeof(int);
 }
 
 hipError_t launch_transport(bool fp32, bool batch, bool defer, int nl, bool regroup, const ProblemK *d_probs,
